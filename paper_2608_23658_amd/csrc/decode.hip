@@ -2,14 +2,29 @@
 // to its whole context, read through the block table (the paper, Section 3
 // "The contiguity constraint"; Section 5, decode is one token per sequence).
 //
-// One workgroup = one wavefront = one (kv head, sequence, split of the
-// context). The grid is one-dimensional with the kv head varying fastest and
+// One workgroup of four wavefronts = one (kv head, sequence, split of the
+// context). The 64-token steps of the split are dealt evenly to the wavefronts
+// (contiguous runs), each keeps its own softmax state, and the states are
+// merged in context order through LDS, so a split costs a quarter of the
+// serial walk it cost as one wavefront. What bounds a small batch is that
+// walk's latency (one step's loads in flight per wavefront); what bounds a
+// large one is HBM. Four wavefronts are at least as fast as one at every size
+// tried, so there is no rule on the batch and a sequence's arithmetic depends
+// only on its own length. Per call, at 1 / 2 / 4 / 8 wavefronts a split
+// (32 query heads over 8 kv heads, head_dim 128, bf16):
+//   1 sequence of 3971 tokens          42 / 25 / 17 / 15 us
+//   8 sequences of 1000 to 2000        50 / 30 / 22 / 19 us
+//   256 sequences of 512 to 4096      402 / 395 / 391 / 410 us
+//   256 sequences of 30 to 300         40 / 36 / 40 / 56 us
+// (giving every wavefront a fixed quarter of 1024 tokens instead of an even
+// share took 55 us on the last). Eight gains 2-3 us on the smallest batches
+// and loses 5% on the full ones. The grid is one-dimensional with the kv head varying fastest and
 // the split slowest, so consecutive workgroups, which the dispatcher deals
 // round-robin to the 8 XCDs, carry equal work: putting the split first would
 // send split k of every sequence to XCD k and starve the XCDs that hold the
 // late splits only long sequences have. The G query heads sharing the kv
 // head are served by every K/V byte read (grouped-query sharing). The
-// wavefront walks its split in steps of 64 tokens (4 blocks of 16):
+// wavefront walks its share in steps of 64 tokens (4 blocks of 16):
 //   * loads: each block's K tile and V tile are read as they lie in memory,
 //     1 KiB per 16-byte load (K and V are read once, so the loads are
 //     non-temporal), and the K and V loads of a block are issued together.
@@ -29,8 +44,8 @@
 //   * V: in the dim-major V tile lane l owns dim rows l / R (R = 16-byte
 //     chunks per row) and a run of consecutive tokens, so for bf16 p.v is a
 //     bf16 dot2 over token pairs. p reaches those lanes through LDS.
-// Only the last step of a split can hold slots past the sequence's length,
-// whose contents are arbitrary (possibly NaN); that step masks them. Partials
+// Only the last step of a sequence can hold slots past its length, whose
+// contents are arbitrary (possibly NaN); a wavefront's last step masks them. Partials
 // (m, l, o) of every split go to the workspace; a second kernel merges them
 // (log-sum-exp) in split order, so the result depends only on the sequence's
 // own length.
@@ -39,6 +54,14 @@
 #include "launch.hpp"
 
 namespace kvattn {
+
+constexpr int kDecodeWaves = 4;   // wavefronts that share one split
+
+// Orders a wavefront's LDS writes before its own later reads by other lanes.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 template <int D, int G, bool BF16>
 struct DecodeShape {
@@ -61,7 +84,9 @@ struct DecodeShape {
 // Section 3, "The contiguity constraint"): ids below num_base address kv, the
 // others kv2 at id - num_base. Otherwise kv2 and num_base are unused.
 template <int D, int G, bool BF16, bool kTwo = false>
-__global__ __launch_bounds__(64) void decode_split_kernel(
+__global__ __attribute__((amdgpu_flat_work_group_size(kDecodeWaves * kWave, kDecodeWaves * kWave),
+                          amdgpu_waves_per_eu(2)))
+void decode_split_kernel(
     const uint8_t* __restrict__ q, const uint8_t* __restrict__ kv,
     const uint8_t* __restrict__ kv2, int num_base, int num_blocks,
     const int* __restrict__ block_table, const int* __restrict__ seq_lens,
@@ -69,11 +94,13 @@ __global__ __launch_bounds__(64) void decode_split_kernel(
     int num_seqs, int num_q_heads, int num_kv_heads, int max_blocks, int max_seq_len,
     int split_tokens, int max_splits, float scale_log2) {
   using S = DecodeShape<D, G, BF16>;
+  constexpr int W = kDecodeWaves;
   const int wid = blockIdx.x;
   const int g = wid % num_kv_heads;
   const int s = (wid / num_kv_heads) % num_seqs;
   const int split = wid / (num_kv_heads * num_seqs);
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int h0 = g * G;
   const size_t row_bytes = (size_t)D * S::kEsz;
 
@@ -84,23 +111,36 @@ __global__ __launch_bounds__(64) void decode_split_kernel(
   if (L == 0) {
     if (split == 0) {
       uint4* o = reinterpret_cast<uint4*>(out + ((size_t)s * num_q_heads + h0) * row_bytes);
-      for (int c = lane; c < G * D * S::kEsz / 16; c += kWave) o[c] = make_uint4(0, 0, 0, 0);
+      for (int c = threadIdx.x; c < G * D * S::kEsz / 16; c += W * kWave)
+        o[c] = make_uint4(0, 0, 0, 0);
     }
     return;
   }
   if (split >= nsplit) return;
-  const int t0 = split * split_tokens;
-  const int t1 = min(L, t0 + split_tokens);
+  const int s0 = split * split_tokens;                       // the workgroup's tokens
+  const int s1 = min(L, s0 + split_tokens);
+  // whole steps, spread evenly over the wavefronts
+  const int part_tokens = ((s1 - s0 + W * S::kTile - 1) / (W * S::kTile)) * S::kTile;
+  const int parts = (s1 - s0 + part_tokens - 1) / part_tokens;   // wavefronts with tokens
+  const int t0 = s0 + wave * part_tokens;                    // this wavefront's tokens
+  const int t1 = min(s1, t0 + part_tokens);
 
-  __shared__ uint32_t p_lds[S::kPWords];
+  __shared__ uint32_t p_lds_all[W][S::kPWords];
   __shared__ uint4 q_lds[G * S::kKCh];
+  uint32_t* p_lds = p_lds_all[wave];
+
+  // The ids of the wavefront's blocks, one per lane (a split has at most 64
+  // blocks): one load instead of one dependent load per step.
+  const int* bt = block_table + (size_t)s * max_blocks;
+  int my_id = -1;
+  if (t0 + lane * S::kBS < t1) my_id = bt[t0 / S::kBS + lane];
   {
     const uint4* qsrc = reinterpret_cast<const uint4*>(q + ((size_t)s * num_q_heads + h0) * row_bytes);
-    for (int i = lane; i < G * S::kKCh; i += kWave) q_lds[i] = qsrc[i];
+    for (int i = threadIdx.x; i < G * S::kKCh; i += W * kWave) q_lds[i] = qsrc[i];
   }
+  if ((unsigned)my_id >= (unsigned)num_blocks) my_id = -1;
   __syncthreads();
 
-  const int* bt = block_table + (size_t)s * max_blocks;
   const size_t tile_bytes = (size_t)S::kTileElems * S::kEsz;
   const size_t head_off = (size_t)g * tile_bytes;
   const size_t block_bytes = 2 * (size_t)num_kv_heads * tile_bytes;
@@ -131,17 +171,10 @@ __global__ __launch_bounds__(64) void decode_split_kernel(
   // block, so tokens at or past t1 are masked.
   for (int tb = t0; tb < t1; tb += S::kTile) {
     const bool kTail = tb + S::kTile > t1;
-    const int blk0 = tb / S::kBS;
+    const int blk0 = (tb - t0) / S::kBS;
     int bid[S::kTB];
 #pragma unroll
-    for (int j = 0; j < S::kTB; ++j) {
-      int id = -1;
-      if (!kTail || tb + j * S::kBS < t1) {
-        id = bt[blk0 + j];
-        if ((unsigned)id >= (unsigned)num_blocks) id = -1;
-      }
-      bid[j] = id;
-    }
+    for (int j = 0; j < S::kTB; ++j) bid[j] = __builtin_amdgcn_readlane(my_id, blk0 + j);
     int my_b = bid[0];
 #pragma unroll
     for (int j = 1; j < S::kTB; ++j) my_b = (kj == j) ? bid[j] : my_b;
@@ -239,7 +272,7 @@ __global__ __launch_bounds__(64) void decode_split_kernel(
     for (int i = 0; i < S::kVI; ++i)
 #pragma unroll
       for (int h = 0; h < G; ++h) acc[i][h] *= alpha[h];
-    __syncthreads();
+    wave_lds_sync();
 
     // ---- p . v ----
 #pragma unroll
@@ -309,7 +342,7 @@ __global__ __launch_bounds__(64) void decode_split_kernel(
         }
       }
     }
-    __syncthreads();
+    wave_lds_sync();
   }
 
   // ---- finish: lane sums, merge the chunks of a dim row ----
@@ -323,31 +356,45 @@ __global__ __launch_bounds__(64) void decode_split_kernel(
 #pragma unroll
       for (int o = 1; o < S::kR; o <<= 1) acc[i][h] += __shfl_xor(acc[i][h], o, kWave);
 
-  if (nsplit == 1) {
+  // ---- merge the wavefronts' states (log-sum-exp, in context order) ----
+  __shared__ float o_lds[W][G][D];
+  __shared__ float2 ml_lds[W][G];
+  if (wave < parts) {
     if (vrc == 0) {
 #pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const float inv = l_tot[h] > 0.f ? 1.f / l_tot[h] : 0.f;
-        uint8_t* orow = out + ((size_t)s * num_q_heads + h0 + h) * row_bytes;
+      for (int h = 0; h < G; ++h)
 #pragma unroll
-        for (int i = 0; i < S::kVI; ++i) {
-          const int d = i * S::kDPI + lane / S::kR;
-          if constexpr (BF16)
-            reinterpret_cast<uint16_t*>(orow)[d] = to_bf16(acc[i][h] * inv);
-          else
-            reinterpret_cast<float*>(orow)[d] = acc[i][h] * inv;
-        }
-      }
+        for (int i = 0; i < S::kVI; ++i) o_lds[wave][h][i * S::kDPI + lane / S::kR] = acc[i][h];
     }
-  } else {
+    if (lane == 0) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
+      for (int h = 0; h < G; ++h) ml_lds[wave][h] = make_float2(m_run[h], l_tot[h]);
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < G * D; e += W * kWave) {
+    const int h = e / D, d = e % D;
+    float m = -INFINITY;
+    for (int j = 0; j < parts; ++j) m = fmaxf(m, ml_lds[j][h].x);
+    const float ref = (m == -INFINITY) ? 0.f : m;
+    float l = 0.f, o = 0.f;
+    for (int j = 0; j < parts; ++j) {
+      const float2 ml = ml_lds[j][h];
+      const float w = fast_exp2(ml.x - ref);
+      l = fmaf(w, ml.y, l);
+      o = fmaf(w, o_lds[j][h][d], o);
+    }
+    if (nsplit == 1) {
+      const float inv = l > 0.f ? 1.f / l : 0.f;
+      uint8_t* orow = out + ((size_t)s * num_q_heads + h0 + h) * row_bytes;
+      if constexpr (BF16)
+        reinterpret_cast<uint16_t*>(orow)[d] = to_bf16(o * inv);
+      else
+        reinterpret_cast<float*>(orow)[d] = o * inv;
+    } else {
       const size_t idx = ((size_t)s * num_q_heads + h0 + h) * max_splits + split;
-      if (vrc == 0) {
-#pragma unroll
-        for (int i = 0; i < S::kVI; ++i) ws_o[idx * D + i * S::kDPI + lane / S::kR] = acc[i][h];
-      }
-      if (lane == 0) ws_ml[idx] = make_float2(m_run[h], l_tot[h]);
+      ws_o[idx * D + d] = o;
+      if (d == 0) ws_ml[idx] = make_float2(m, l);
     }
   }
 }
@@ -404,8 +451,8 @@ static hipError_t launch_decode_t(const DecodeArgs& a) {
   float* ws_o = reinterpret_cast<float*>(a.workspace);
   float2* ws_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(a.workspace) + a.ws_ml_offset);
   trace_before(a.stream, kTwo ? "decode_split_two_tensor" : "decode_split");
-  hipLaunchKernelGGL((decode_split_kernel<D, G, BF16, kTwo>), dim3((unsigned)blocks), dim3(64), 0,
-                     a.stream, static_cast<const uint8_t*>(a.q),
+  hipLaunchKernelGGL((decode_split_kernel<D, G, BF16, kTwo>), dim3((unsigned)blocks),
+                     dim3(kDecodeWaves * kWave), 0, a.stream, static_cast<const uint8_t*>(a.q),
                      static_cast<const uint8_t*>(a.kv), static_cast<const uint8_t*>(a.kv2),
                      a.num_base, a.num_blocks, a.block_table, a.seq_lens,
                      static_cast<uint8_t*>(a.out), ws_o, ws_ml, a.num_seqs, a.num_q_heads,

@@ -1,0 +1,72 @@
+"""The wavefronts of a decode split: the split's 64-token steps are shared by
+four wavefronts whose softmax states are merged. Lengths sit on the edges of
+the shares, and a sequence must come out the same alone as in a batch."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_23658_amd.kvattn as K
+from workloads import make_batch_from_lens
+from tests.gpu_helpers import Dev, assert_parity, oracle_decode, require_gpu, say, seq_bounds
+
+pytestmark = pytest.mark.gpu
+
+# one step per wavefront, one more than that, uneven shares, whole splits
+EDGES = [1, 64, 65, 128, 129, 192, 193, 256, 257, 320, 321, 512, 513, 960, 961, 1024, 1025,
+         1088, 1089, 1280, 2047]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def _batch(lens, hq, hkv, d, dtype, seed):
+    return make_batch_from_lens(lens, [1] * len(lens), dtype=dtype, num_q_heads=hq,
+                                num_kv_heads=hkv, head_dim=d, block_size=16, seed=seed)
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 1, 128, "bf16"), (4, 4, 128, "bf16"),
+                                            (16, 2, 64, "bf16"), (8, 2, 64, "f32")])
+def test_share_edges(hq, hkv, d, dtype):
+    b = _batch(EDGES, hq, hkv, d, dtype, seed=211)
+    say("decode share edges", hq, hkv, d, dtype)
+    out = Dev(b).decode()
+    torch.cuda.synchronize()
+    assert_parity(out, oracle_decode(b), dtype, f"share edges {hq}/{hkv}/{d}/{dtype}",
+                  seq_bounds(b, decode=True))
+
+
+def test_a_sequence_does_not_depend_on_its_batch():
+    """Every sequence decoded on its own, with its own length as max_seq_len,
+    gives the bits it gives in a batch with a far longer one."""
+    b = _batch(EDGES + [9300], 8, 2, 128, "bf16", seed=212)
+    dev = Dev(b)
+    say("decode batch independence")
+    whole = dev.decode()
+    for s, L in enumerate(b.seq_lens.tolist()):
+        one = K.decode(dev.q[s:s + 1], dev.kv, b.num_blocks, dev.bt[s:s + 1].contiguous(),
+                       dev.sl[s:s + 1].contiguous(), num_kv_heads=2, max_seq_len=L,
+                       scale=b.scale)
+        assert torch.equal(one[0].view(torch.int16), whole[s].view(torch.int16)), L
+
+
+def test_a_share_without_valid_blocks_contributes_nothing():
+    """All blocks of one wavefront's share carry ids outside the layer; the
+    result is that of the sequence without those tokens."""
+    b = _batch([1024], 4, 1, 128, "bf16", seed=213)
+    dev = Dev(b)
+    keep = np.r_[0:16, 32:64]                      # blocks of shares 0, 2 and 3
+    holes = dev.bt.clone()
+    holes[0, 16:32] = b.num_blocks
+    short = torch.full_like(dev.bt, -1)
+    short[0, :48] = dev.bt[0, torch.from_numpy(keep).cuda()]
+    say("decode share without valid blocks")
+    kw = dict(num_kv_heads=1, scale=b.scale)
+    got = K.decode(dev.q, dev.kv, b.num_blocks, holes, dev.sl, max_seq_len=1024, **kw)
+    want = K.decode(dev.q, dev.kv, b.num_blocks, short, torch.full_like(dev.sl, 768),
+                    max_seq_len=1024, **kw)
+    assert torch.isfinite(got).all()
+    # the two order their sums differently: P rounded to bf16 against different maxima
+    d = (got.float() - want.float()).norm() / want.float().norm()
+    assert d < 1e-2, float(d)
