@@ -70,3 +70,20 @@ def test_a_share_without_valid_blocks_contributes_nothing():
     # the two order their sums differently: P rounded to bf16 against different maxima
     d = (got.float() - want.float()).norm() / want.float().norm()
     assert d < 1e-2, float(d)
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(4, 1, 64, "bf16"), (2, 2, 128, "bf16"),
+                                            (2, 1, 64, "f32")])
+def test_combine_split_counts(hq, hkv, d, dtype):
+    """1, 2, 8 (one wavefront), 9, 31, 32, 33 and 65 to 69 splits (shared by
+    four wavefronts, with and without a remainder) in one batch and, for the
+    lengths one wavefront merges, in a batch that has no longer ones."""
+    lens = [1000, 1025, 8192, 8193, 31 * 1024, 32 * 1024, 32 * 1024 + 1, 65 * 1024 + 5,
+            69 * 1024]
+    for sel in (lens, lens[:3]):
+        b = _batch(sel, hq, hkv, d, dtype, seed=214)
+        say("decode combine", hq, hkv, d, dtype, sel)
+        out = Dev(b).decode()
+        torch.cuda.synchronize()
+        assert_parity(out, oracle_decode(b), dtype, f"combine {hq}/{hkv}/{d}/{dtype}",
+                      seq_bounds(b, decode=True))
