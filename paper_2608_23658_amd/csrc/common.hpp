@@ -31,6 +31,8 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float acc) {
                                          __builtin_bit_cast(bf16x2_t, b), acc, false);
 }
 
+constexpr uint32_t kBf16OnePair = 0x3f803f80u;   // (1.0, 1.0) in bf16
+
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
 // 16-byte load marked non-temporal: data read once streams past the caches.
@@ -52,23 +54,16 @@ constexpr int kDppQuadSwap2 = 0x4e;       // quad_perm [2, 3, 0, 1]
 constexpr int kDppRowHalfMirror = 0x141;  // lane i <-> 7 - i within each 8 lanes
 constexpr int kDppRowMirror = 0x140;      // lane i <-> 15 - i within each 16 lanes
 
-// Max / sum over all 64 lanes, result in every lane: four DPP steps inside
-// each row of 16 lanes, then the gfx950 row swaps (rows 0<->1 and 2<->3, then
-// the two halves of the wavefront).
-__device__ __forceinline__ float wave_max(float x) {
-  x = fmaxf(x, dpp_mov<kDppQuadSwap1>(x));
-  x = fmaxf(x, dpp_mov<kDppQuadSwap2>(x));
-  x = fmaxf(x, dpp_mov<kDppRowHalfMirror>(x));
-  x = fmaxf(x, dpp_mov<kDppRowMirror>(x));
-  const uint32_t u = __float_as_uint(x);
-  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  x = fmaxf(__uint_as_float(r16[0]), __uint_as_float(r16[1]));
-  const uint32_t v = __float_as_uint(x);
-  const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return fmaxf(__uint_as_float(r32[0]), __uint_as_float(r32[1]));
+// Exchanges lane rows 1 and 3 of a with lane rows 0 and 2 of b: a becomes
+// (a0, b0, a2, b2) and b (a1, b1, a3, b3), rows of 16 lanes.
+__device__ __forceinline__ void swap_rows16(uint32_t& a, uint32_t& b) {
+  const auto e = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = e[0];
+  b = e[1];
 }
-// Sum over lanes l, l ^ 16, l ^ 32 and l ^ 48 (the same lane of each row of
-// 16), in every lane: the gfx950 row swaps (rows 0<->1 and 2<->3, then the
+
+// Sum / max over lanes l, l ^ 16, l ^ 32 and l ^ 48 (the same lane of each row
+// of 16), in every lane: the gfx950 row swaps (rows 0<->1 and 2<->3, then the
 // two halves of the wavefront). The four lanes get bit-identical results.
 __device__ __forceinline__ float cross_row_sum(float x) {
   const uint32_t u = __float_as_uint(x);
@@ -78,17 +73,31 @@ __device__ __forceinline__ float cross_row_sum(float x) {
   const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
 }
+__device__ __forceinline__ float cross_row_max(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = fmaxf(__uint_as_float(r16[0]), __uint_as_float(r16[1]));
+  const uint32_t v = __float_as_uint(x);
+  const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return fmaxf(__uint_as_float(r32[0]), __uint_as_float(r32[1]));
+}
+
+// Max / sum over all 64 lanes, result in every lane: four DPP steps inside
+// each row of 16 lanes, then the gfx950 row swaps (rows 0<->1 and 2<->3, then
+// the two halves of the wavefront).
+__device__ __forceinline__ float wave_max(float x) {
+  x = fmaxf(x, dpp_mov<kDppQuadSwap1>(x));
+  x = fmaxf(x, dpp_mov<kDppQuadSwap2>(x));
+  x = fmaxf(x, dpp_mov<kDppRowHalfMirror>(x));
+  x = fmaxf(x, dpp_mov<kDppRowMirror>(x));
+  return cross_row_max(x);
+}
 __device__ __forceinline__ float wave_sum(float x) {
   x += dpp_mov<kDppQuadSwap1>(x);
   x += dpp_mov<kDppQuadSwap2>(x);
   x += dpp_mov<kDppRowHalfMirror>(x);
   x += dpp_mov<kDppRowMirror>(x);
-  const uint32_t u = __float_as_uint(x);
-  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  x = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
-  const uint32_t v = __float_as_uint(x);
-  const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+  return cross_row_sum(x);
 }
 
 }  // namespace kvattn

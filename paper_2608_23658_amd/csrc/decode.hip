@@ -9,46 +9,44 @@
 // serial walk it cost as one wavefront. What bounds a small batch is that
 // walk's latency (one step's loads in flight per wavefront); what bounds a
 // large one is HBM. Four wavefronts are at least as fast as one at every size
-// tried, so there is no rule on the batch and a sequence's arithmetic depends
+// tried, so there is no rule on the batch, and a sequence's arithmetic depends
 // only on its own length. Per call, at 1 / 2 / 4 / 8 wavefronts a split
 // (32 query heads over 8 kv heads, head_dim 128, bf16):
 //   1 sequence of 3971 tokens          42 / 25 / 17 / 15 us
 //   8 sequences of 1000 to 2000        50 / 30 / 22 / 19 us
 //   256 sequences of 512 to 4096      402 / 395 / 391 / 410 us
 //   256 sequences of 30 to 300         40 / 36 / 40 / 56 us
-// (giving every wavefront a fixed quarter of 1024 tokens instead of an even
-// share took 55 us on the last). Eight gains 2-3 us on the smallest batches
-// and loses 5% on the full ones. The grid is one-dimensional with the kv head varying fastest and
-// the split slowest, so consecutive workgroups, which the dispatcher deals
-// round-robin to the 8 XCDs, carry equal work: putting the split first would
-// send split k of every sequence to XCD k and starve the XCDs that hold the
-// late splits only long sequences have. The G query heads sharing the kv
-// head are served by every K/V byte read (grouped-query sharing). The
-// wavefront walks its share in steps of 64 tokens (4 blocks of 16):
-//   * loads: each block's K tile and V tile are read as they lie in memory,
-//     1 KiB per 16-byte load (K and V are read once, so the loads are
-//     non-temporal), and the K and V loads of a block are issued together.
-//     Reading K lane-per-token instead (four 256-byte pieces from four blocks
-//     per load), or all K loads before all V loads, measured 4-6% slower:
-//     the memory system serves a block's two tiles best when they are asked
-//     for at once.
-//   * K: with the chunk-major K tile, load i of a block gives lane l chunk
-//     4 i + l / 16 of token slot l % 16, a quarter of that token's row. Each
-//     lane dots its quarters of the rows of the four tokens in its slot (one
-//     per block) with the same dims of q (read from LDS), and the four lanes
-//     of a slot add their quarters with two row swaps. Lane t then takes the
-//     score of token t of the step (block t / 16, slot t % 16).
-//   * softmax: wavefront max per head (DPP and lane-row swaps), exp2 in the
-//     log2 domain, lane-local partial sums, one rescale of the accumulators
-//     per step.
-//   * V: in the dim-major V tile lane l owns dim rows l / R (R = 16-byte
-//     chunks per row) and a run of consecutive tokens, so for bf16 p.v is a
-//     bf16 dot2 over token pairs. p reaches those lanes through LDS.
+// (measured with q.k and p.v on the vector unit; giving every wavefront a fixed
+// quarter of 1024 tokens instead of an even share took 55 us on the last).
+// Eight gains 2-3 us on the smallest batches and loses 5% on the full ones.
+//
+// The grid is one-dimensional with the kv head varying fastest and the split
+// slowest, so consecutive workgroups, which the dispatcher deals round-robin to
+// the 8 XCDs, carry equal work: putting the split first would send split k of
+// every sequence to XCD k and starve the XCDs that hold the late splits only
+// long sequences have. The G query heads sharing the kv head are served by
+// every K/V byte read (grouped-query sharing).
+//
+// A wavefront walks its share in steps of 64 tokens (4 blocks of 16). Each
+// block's K tile and V tile are read as they lie in memory, 1 KiB per 16-byte
+// load (K and V are read once, so the loads are non-temporal), and the K and V
+// loads of a block are issued together. Reading K lane-per-token instead (four
+// 256-byte pieces from four blocks per load), or all K loads before all V
+// loads, measured 4-6% slower: the memory system serves a block's two tiles
+// best when they are asked for at once. The step's products and softmax (log2
+// domain) follow once its loads have landed: bf16 on the matrix units
+// (walk_bf16), fp32 on the vector unit (walk_f32). The vector form of the bf16
+// walk was itself the limit at 8 query heads per kv head and a third of a
+// step's latency at 4; against it the matrix form took, per call,
+//   64 sequences of 512 to 4096, 64 query heads over 8, head_dim 128: 111 -> 96 us
+//   12 sequences of 1 to 4096, 64 over 8, head_dim 64:                 31 -> 18 us
+//   1 sequence of 3971, 32 over 8, head_dim 128:                     20.5 -> 16 us
+//   256 sequences of 512 to 4096, 32 over 8, head_dim 128 (HBM-bound): 391 -> 387 us
+//
 // Only the last step of a sequence can hold slots past its length, whose
-// contents are arbitrary (possibly NaN); a wavefront's last step masks them. Partials
-// (m, l, o) of every split go to the workspace; a second kernel merges them
-// (log-sum-exp) in split order, so the result depends only on the sequence's
-// own length.
+// contents are arbitrary (possibly NaN); a wavefront's last step masks them.
+// Partials (m, l, o) of every split go to the workspace; a second kernel merges
+// them (log-sum-exp), in an order that depends only on the sequence's length.
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -63,7 +61,7 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int D, int G, bool BF16>
+template <int D, bool BF16>
 struct DecodeShape {
   static constexpr int kEsz = BF16 ? 2 : 4;
   static constexpr int kVec = 16 / kEsz;          // elements per 16-byte chunk
@@ -75,14 +73,338 @@ struct DecodeShape {
   static constexpr int kDPI = kWave / kR;         // V dim rows per load
   static constexpr int kVI = D / kDPI;            // V loads per block
   static constexpr int kTileElems = kBS * D;      // one (block, K/V, head) tile
-  static constexpr int kPWords = BF16 ? (kTile / 2) * G : kTile * G;
   static_assert(kVI * 1024 == kTileElems * kEsz, "V tile is kVI loads of 1 KiB");
   static_assert(kKCh == 4 * kVI, "a K load of 1 KiB holds a quarter of each of 16 rows");
 };
 
+// Where a workgroup's K and V tiles lie.
 // kTwo: the layer is split over two tensors (the design the paper rejects in
 // Section 3, "The contiguity constraint"): ids below num_base address kv, the
 // others kv2 at id - num_base. Otherwise kv2 and num_base are unused.
+template <bool kTwo>
+struct DecodeTiles {
+  const uint8_t* kv;
+  const uint8_t* kv2;
+  int num_base;
+  size_t block_bytes, k_off, v_off;
+  __device__ __forceinline__ const uint8_t* block(int id) const {
+    if constexpr (kTwo)
+      return id < num_base ? kv + (size_t)id * block_bytes
+                           : kv2 + (size_t)(id - num_base) * block_bytes;
+    else
+      return kv + (size_t)id * block_bytes;
+  }
+};
+
+// The four blocks of a step: each block's K tile and V tile as they lie in
+// memory, 1 KiB per load, the two tiles of a block issued together. Within a
+// V load lane l takes 16-byte chunk v_lane of the KiB. A block without a valid
+// id (< 0) gives zeros.
+template <int kTB, int kVI, bool kTwo>
+__device__ __forceinline__ void load_step(const DecodeTiles<kTwo>& t, const int (&bid)[kTB],
+                                          int lane, int v_lane, uint4 (&kreg)[kTB][kVI],
+                                          uint4 (&vreg)[kTB][kVI]) {
+#pragma unroll
+  for (int j = 0; j < kTB; ++j) {
+    if (bid[j] >= 0) {
+      const uint8_t* bp = t.block(bid[j]);
+      const uint4* kp = reinterpret_cast<const uint4*>(bp + t.k_off) + lane;
+      const uint4* vp = reinterpret_cast<const uint4*>(bp + t.v_off) + v_lane;
+#pragma unroll
+      for (int i = 0; i < kVI; ++i) {
+        kreg[j][i] = load_nt(kp + i * kWave);
+        vreg[j][i] = load_nt(vp + i * kWave);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < kVI; ++i) {
+        kreg[j][i] = make_uint4(0, 0, 0, 0);
+        vreg[j][i] = make_uint4(0, 0, 0, 0);
+      }
+    }
+  }
+}
+
+// One wavefront's walk over tokens [t0, t1) in bf16, on the matrix units: with
+// query heads as the 16 columns (G of them real, the rest zero), a step is 16
+// products of 16 x 16 x 32 for q.k and 16 for p.v at head_dim 128, whatever G
+// is, where bf16 dot2 on the vector unit took 128 G instructions per step.
+//   S[token][head]: A = a KiB of the K tile exactly as loaded (lane l: slot
+//     l % 16, chunk 4 i + l / 16), B = q in registers. Lane l gets tokens
+//     4 (l / 16) .. + 4 of each block for head l % 16, so the softmax state is
+//     per lane and one row exchange gives the max.
+//   O^T[dim][head] += V^T P^T over 32 tokens, two blocks: the B operand needs 8
+//     consecutive tokens per lane, which one swap of the odd lane rows of the
+//     first block's P with the even rows of the second's gives; the same swap
+//     of the two blocks' V loads gives the matching A operands of 16 dims each.
+// my_id: lane l holds the id of the walk's block l (-1: none). Leaves the
+// wavefront's state in o_out [G][D] and ml_out [G] (LDS).
+template <int D, int G, bool kTwo>
+__device__ __forceinline__ void walk_bf16(const DecodeTiles<kTwo>& tiles,
+                                          const uint16_t* __restrict__ q, int my_id, int t0,
+                                          int t1, float scale_log2, float* o_out,
+                                          float2* ml_out) {
+  using S = DecodeShape<D, true>;
+  const int lane = threadIdx.x % kWave;
+  const int head = lane % 16, row = lane / 16;
+  uint4 qreg[S::kVI];
+#pragma unroll
+  for (int i = 0; i < S::kVI; ++i) {
+    qreg[i] = *reinterpret_cast<const uint4*>(q + min(head, G - 1) * D + i * 32 + row * 8);
+    if (head >= G) qreg[i] = make_uint4(0, 0, 0, 0);
+  }
+
+  float m_run = -INFINITY, l_run = 0.f;   // head's max; the lane's part of its sum
+  f32x4_t acc[2 * S::kVI];
+#pragma unroll
+  for (int i = 0; i < 2 * S::kVI; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // lane's 16 bytes of a V KiB (32 dims x 2 halves): dim l % 32, half l / 32
+  const int v_lane = 2 * (lane % 32) + lane / 32;
+
+  for (int tb = t0; tb < t1; tb += S::kTile) {
+    const bool tail = tb + S::kTile > t1;   // the step may end inside a block
+    int bid[S::kTB];
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j)
+      bid[j] = __builtin_amdgcn_readlane(my_id, (tb - t0) / S::kBS + j);
+    uint4 kreg[S::kTB][S::kVI], vreg[S::kTB][S::kVI];
+    load_step(tiles, bid, lane, v_lane, kreg, vreg);
+
+    // ---- scores ----
+    float x[S::kTB][4];
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j) {
+      f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < S::kVI; ++i)
+        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kreg[j][i]),
+                                                     __builtin_bit_cast(bf16x8_t, qreg[i]), sc, 0,
+                                                     0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool keep = bid[j] >= 0 && (!tail || tb + j * S::kBS + row * 4 + r < t1);
+        x[j][r] = keep ? sc[r] * scale_log2 : -INFINITY;
+      }
+    }
+
+    // ---- online softmax over the step (log2 domain) ----
+    float mx = m_run;
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx = fmaxf(mx, x[j][r]);
+    const float mn = cross_row_max(mx);
+    const float ref = (mn == -INFINITY) ? 0.f : mn;
+    const float alpha = fast_exp2(m_run - ref);
+    m_run = mn;
+    float psum = 0.f;
+    uint2 pw[S::kTB];
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j) {
+      pw[j].x = pack_bf16x2(fast_exp2(x[j][0] - ref), fast_exp2(x[j][1] - ref));
+      pw[j].y = pack_bf16x2(fast_exp2(x[j][2] - ref), fast_exp2(x[j][3] - ref));
+      // the row sum adds the bf16 values that p.v multiplies
+      psum = dot2_bf16(pw[j].x, kBf16OnePair, psum);
+      psum = dot2_bf16(pw[j].y, kBf16OnePair, psum);
+    }
+    l_run = fmaf(l_run, alpha, psum);
+#pragma unroll
+    for (int i = 0; i < 2 * S::kVI; ++i) acc[i] *= alpha;
+
+    // ---- p . v, two blocks at a time ----
+    if (tail) {
+#pragma unroll
+      for (int j = 0; j < S::kTB; ++j) {
+        // slots at or past t1 may hold anything, and zero times NaN is NaN
+        const int tok = tb + j * S::kBS + (lane / 32) * 8;
+#pragma unroll
+        for (int i = 0; i < S::kVI; ++i) {
+          uint32_t w[4] = {vreg[j][i].x, vreg[j][i].y, vreg[j][i].z, vreg[j][i].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t lo = (tok + 2 * k < t1) ? 0x0000ffffu : 0u;
+            const uint32_t hi = (tok + 2 * k + 1 < t1) ? 0xffff0000u : 0u;
+            w[k] &= (lo | hi);
+          }
+          vreg[j][i] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < S::kTB; j += 2) {
+      uint2 p0 = pw[j], p1 = pw[j + 1];
+      swap_rows16(p0.x, p1.x);
+      swap_rows16(p0.y, p1.y);
+      const bf16x8_t b = __builtin_bit_cast(bf16x8_t, make_uint4(p0.x, p0.y, p1.x, p1.y));
+#pragma unroll
+      for (int i = 0; i < S::kVI; ++i) {
+        uint4 lo = vreg[j][i], hi = vreg[j + 1][i];
+        swap_rows16(lo.x, hi.x);   // dims 32 i .. + 16 to lo, 32 i + 16 .. + 16 to hi
+        swap_rows16(lo.y, hi.y);
+        swap_rows16(lo.z, hi.z);
+        swap_rows16(lo.w, hi.w);
+        acc[2 * i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8_t, lo), b, acc[2 * i], 0, 0, 0);
+        acc[2 * i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8_t, hi), b, acc[2 * i + 1], 0, 0, 0);
+      }
+    }
+  }
+
+  const float l_tot = cross_row_sum(l_run);
+  if (head < G) {
+#pragma unroll
+    for (int i = 0; i < 2 * S::kVI; ++i)
+      *reinterpret_cast<f32x4_t*>(o_out + head * D + i * 16 + row * 4) = acc[i];
+    if (row == 0) ml_out[head] = make_float2(m_run, l_tot);
+  }
+}
+
+// The same in fp32 on the vector unit. Each lane dots its quarter of the rows
+// of the four tokens in its slot (one per block) with the same dims of q (read
+// from LDS), and the four lanes of a slot add their quarters with two row
+// swaps; lane t then takes the score of token t of the step. In the dim-major V
+// tile lane l owns dim rows l / R (R = 16-byte chunks per row) and a run of
+// consecutive tokens, whose p reach it through LDS.
+template <int D, int G>
+__device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const uint4* q_lds,
+                                         float* p_lds, int my_id, int t0, int t1,
+                                         float scale_log2, float* o_out, float2* ml_out) {
+  using S = DecodeShape<D, false>;
+  const int lane = threadIdx.x % kWave;
+  float m_run[G], l_run[G], acc[S::kVI][G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    m_run[h] = -INFINITY;
+    l_run[h] = 0.f;
+#pragma unroll
+    for (int i = 0; i < S::kVI; ++i) acc[i][h] = 0.f;
+  }
+  // block of this lane's token within the step, and which quarter of the K
+  // rows of its slot the lane holds
+  const int kj = lane / S::kBS;
+  const int vrc = lane % S::kR;   // this lane's chunk of a V dim row
+
+  for (int tb = t0; tb < t1; tb += S::kTile) {
+    const bool tail = tb + S::kTile > t1;   // the step may end inside a block
+    int bid[S::kTB];
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j)
+      bid[j] = __builtin_amdgcn_readlane(my_id, (tb - t0) / S::kBS + j);
+    int my_b = bid[0];
+#pragma unroll
+    for (int j = 1; j < S::kTB; ++j) my_b = (kj == j) ? bid[j] : my_b;
+    const bool kvalid = (!tail || tb + lane < t1) && (my_b >= 0);
+    uint4 kreg[S::kTB][S::kVI], vreg[S::kTB][S::kVI];
+    load_step(tiles, bid, lane, lane, kreg, vreg);
+
+    // ---- scores ----
+    float part[S::kTB][G];
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j)
+#pragma unroll
+      for (int h = 0; h < G; ++h) part[j][h] = 0.f;
+#pragma unroll
+    for (int i = 0; i < S::kVI; ++i) {
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        const uint4 qc = q_lds[h * S::kKCh + 4 * i + kj];
+#pragma unroll
+        for (int j = 0; j < S::kTB; ++j) {
+          const uint4 k = kreg[j][i];
+          float a = part[j][h];
+          a = fmaf(__uint_as_float(k.x), __uint_as_float(qc.x), a);
+          a = fmaf(__uint_as_float(k.y), __uint_as_float(qc.y), a);
+          a = fmaf(__uint_as_float(k.z), __uint_as_float(qc.z), a);
+          a = fmaf(__uint_as_float(k.w), __uint_as_float(qc.w), a);
+          part[j][h] = a;
+        }
+      }
+    }
+    // this lane's token is slot lane % 16 of block kj
+    float sc[G];
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+#pragma unroll
+      for (int j = 0; j < S::kTB; ++j) part[j][h] = cross_row_sum(part[j][h]);
+      sc[h] = part[0][h];
+#pragma unroll
+      for (int j = 1; j < S::kTB; ++j) sc[h] = (kj == j) ? part[j][h] : sc[h];
+    }
+
+    // ---- online softmax over the step (log2 domain) ----
+    float alpha[G];
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const float x = kvalid ? sc[h] * scale_log2 : -INFINITY;
+      const float mn = fmaxf(m_run[h], wave_max(x));
+      const float ref = (mn == -INFINITY) ? 0.f : mn;
+      alpha[h] = fast_exp2(m_run[h] - ref);
+      const float p = fast_exp2(x - ref);
+      p_lds[lane * G + h] = p;
+      l_run[h] = l_run[h] * alpha[h] + p;
+      m_run[h] = mn;
+    }
+#pragma unroll
+    for (int i = 0; i < S::kVI; ++i)
+#pragma unroll
+      for (int h = 0; h < G; ++h) acc[i][h] *= alpha[h];
+    wave_lds_sync();
+
+    // ---- p . v ----
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j) {
+      if (bid[j] < 0) continue;
+      const int tok0 = tb + j * S::kBS + vrc * S::kVec;   // first token of this lane's chunk
+      float pf[4][G];
+      const float* pp = p_lds + (j * S::kBS + vrc * 4) * G;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int h = 0; h < G; ++h) pf[k][h] = pp[k * G + h];
+#pragma unroll
+      for (int i = 0; i < S::kVI; ++i) {
+        const uint4 v = vreg[j][i];
+        float vf[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
+                       __uint_as_float(v.w)};
+        if (tail) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) vf[k] = (tok0 + k < t1) ? vf[k] : 0.f;
+        }
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          float a = acc[i][h];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) a = fmaf(pf[k][h], vf[k], a);
+          acc[i][h] = a;
+        }
+      }
+    }
+    wave_lds_sync();
+  }
+
+  // lane sums, merge the chunks of a dim row
+  float l_tot[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) l_tot[h] = wave_sum(l_run[h]);
+#pragma unroll
+  for (int i = 0; i < S::kVI; ++i)
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int o = 1; o < S::kR; o <<= 1) acc[i][h] += __shfl_xor(acc[i][h], o, kWave);
+  if (vrc == 0) {
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int i = 0; i < S::kVI; ++i) o_out[h * D + i * S::kDPI + lane / S::kR] = acc[i][h];
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int h = 0; h < G; ++h) ml_out[h] = make_float2(m_run[h], l_tot[h]);
+  }
+}
+
 template <int D, int G, bool BF16, bool kTwo = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(kDecodeWaves * kWave, kDecodeWaves * kWave),
                           amdgpu_waves_per_eu(2)))
@@ -93,7 +415,7 @@ void decode_split_kernel(
     uint8_t* __restrict__ out, float* __restrict__ ws_o, float2* __restrict__ ws_ml,
     int num_seqs, int num_q_heads, int num_kv_heads, int max_blocks, int max_seq_len,
     int split_tokens, int max_splits, float scale_log2) {
-  using S = DecodeShape<D, G, BF16>;
+  using S = DecodeShape<D, BF16>;
   constexpr int W = kDecodeWaves;
   const int wid = blockIdx.x;
   const int g = wid % num_kv_heads;
@@ -125,253 +447,38 @@ void decode_split_kernel(
   const int t0 = s0 + wave * part_tokens;                    // this wavefront's tokens
   const int t1 = min(s1, t0 + part_tokens);
 
-  __shared__ uint32_t p_lds_all[W][S::kPWords];
-  __shared__ uint4 q_lds[G * S::kKCh];
-  uint32_t* p_lds = p_lds_all[wave];
-
   // The ids of the wavefront's blocks, one per lane (a split has at most 64
   // blocks): one load instead of one dependent load per step.
   const int* bt = block_table + (size_t)s * max_blocks;
   int my_id = -1;
   if (t0 + lane * S::kBS < t1) my_id = bt[t0 / S::kBS + lane];
-  {
-    const uint4* qsrc = reinterpret_cast<const uint4*>(q + ((size_t)s * num_q_heads + h0) * row_bytes);
-    for (int i = threadIdx.x; i < G * S::kKCh; i += W * kWave) q_lds[i] = qsrc[i];
-  }
   if ((unsigned)my_id >= (unsigned)num_blocks) my_id = -1;
-  __syncthreads();
 
   const size_t tile_bytes = (size_t)S::kTileElems * S::kEsz;
   const size_t head_off = (size_t)g * tile_bytes;
-  const size_t block_bytes = 2 * (size_t)num_kv_heads * tile_bytes;
-  const size_t v_off = (size_t)num_kv_heads * tile_bytes + head_off;
-  auto block_ptr = [&](int id) -> const uint8_t* {
-    if constexpr (kTwo)
-      return id < num_base ? kv + (size_t)id * block_bytes
-                           : kv2 + (size_t)(id - num_base) * block_bytes;
-    else
-      return kv + (size_t)id * block_bytes;
-  };
+  const DecodeTiles<kTwo> tiles = {kv, kv2, num_base, 2 * (size_t)num_kv_heads * tile_bytes,
+                                   head_off, (size_t)num_kv_heads * tile_bytes + head_off};
+  const uint8_t* q_row = q + ((size_t)s * num_q_heads + h0) * row_bytes;
 
-  float m_run[G], l_run[G], acc[S::kVI][G];
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    m_run[h] = -INFINITY;
-    l_run[h] = 0.f;
-#pragma unroll
-    for (int i = 0; i < S::kVI; ++i) acc[i][h] = 0.f;
-  }
-
-  // block of this lane's token within the step, and which quarter of the K
-  // rows of its slot the lane holds
-  const int kj = lane / S::kBS;
-  const int vrc = lane % S::kR;   // this lane's chunk of a V dim row
-
-  // Steps of 64 tokens; in the last one (kTail) the step may end inside a
-  // block, so tokens at or past t1 are masked.
-  for (int tb = t0; tb < t1; tb += S::kTile) {
-    const bool kTail = tb + S::kTile > t1;
-    const int blk0 = (tb - t0) / S::kBS;
-    int bid[S::kTB];
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j) bid[j] = __builtin_amdgcn_readlane(my_id, blk0 + j);
-    int my_b = bid[0];
-#pragma unroll
-    for (int j = 1; j < S::kTB; ++j) my_b = (kj == j) ? bid[j] : my_b;
-    const bool kvalid = (!kTail || tb + lane < t1) && (my_b >= 0);
-
-    // ---- loads: each block's K tile and V tile as they lie in memory, 1 KiB
-    // per load, the two tiles of a block issued together ----
-    // K piece i of a block gives lane l the 16-byte chunk 4 i + l / 16 of the
-    // block's token slot l % 16: a quarter of that token's row.
-    uint4 kreg[S::kTB][S::kVI];
-    uint4 vreg[S::kTB][S::kVI];
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j) {
-      if (bid[j] >= 0) {
-        const uint8_t* bp = block_ptr(bid[j]);
-        const uint4* kp = reinterpret_cast<const uint4*>(bp + head_off) + lane;
-        const uint4* vp = reinterpret_cast<const uint4*>(bp + v_off) + lane;
-#pragma unroll
-        for (int i = 0; i < S::kVI; ++i) {
-          kreg[j][i] = load_nt(kp + i * kWave);
-          vreg[j][i] = load_nt(vp + i * kWave);
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < S::kVI; ++i) {
-          kreg[j][i] = make_uint4(0, 0, 0, 0);
-          vreg[j][i] = make_uint4(0, 0, 0, 0);
-        }
-      }
-    }
-
-    // ---- scores: each lane dots its quarter of the rows of the four tokens
-    // in its slot (one per block) with the same dims of q, then the four
-    // lanes of a slot (l, l ^ 16, l ^ 32, l ^ 48) add their quarters ----
-    float part[S::kTB][G];
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j)
-#pragma unroll
-      for (int h = 0; h < G; ++h) part[j][h] = 0.f;
-#pragma unroll
-    for (int i = 0; i < S::kVI; ++i) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const uint4 qc = q_lds[h * S::kKCh + 4 * i + kj];
-#pragma unroll
-        for (int j = 0; j < S::kTB; ++j) {
-          const uint4 k = kreg[j][i];
-          float a = part[j][h];
-          if constexpr (BF16) {
-            a = dot2_bf16(k.x, qc.x, a);
-            a = dot2_bf16(k.y, qc.y, a);
-            a = dot2_bf16(k.z, qc.z, a);
-            a = dot2_bf16(k.w, qc.w, a);
-          } else {
-            a = fmaf(__uint_as_float(k.x), __uint_as_float(qc.x), a);
-            a = fmaf(__uint_as_float(k.y), __uint_as_float(qc.y), a);
-            a = fmaf(__uint_as_float(k.z), __uint_as_float(qc.z), a);
-            a = fmaf(__uint_as_float(k.w), __uint_as_float(qc.w), a);
-          }
-          part[j][h] = a;
-        }
-      }
-    }
-    // this lane's token is slot lane % 16 of block kj
-    float sc[G];
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-#pragma unroll
-      for (int j = 0; j < S::kTB; ++j) part[j][h] = cross_row_sum(part[j][h]);
-      sc[h] = part[0][h];
-#pragma unroll
-      for (int j = 1; j < S::kTB; ++j) sc[h] = (kj == j) ? part[j][h] : sc[h];
-    }
-
-    // ---- online softmax over the step (log2 domain) ----
-    float alpha[G];
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float x = kvalid ? sc[h] * scale_log2 : -INFINITY;
-      const float mn = fmaxf(m_run[h], wave_max(x));
-      const float ref = (mn == -INFINITY) ? 0.f : mn;
-      alpha[h] = fast_exp2(m_run[h] - ref);
-      float p = fast_exp2(x - ref);
-      if constexpr (BF16) {
-        const uint16_t pb = to_bf16(p);
-        p = __uint_as_float((uint32_t)pb << 16);
-        reinterpret_cast<uint16_t*>(p_lds)[((lane >> 1) * G + h) * 2 + (lane & 1)] = pb;
-      } else {
-        reinterpret_cast<float*>(p_lds)[lane * G + h] = p;
-      }
-      l_run[h] = l_run[h] * alpha[h] + p;
-      m_run[h] = mn;
-    }
-#pragma unroll
-    for (int i = 0; i < S::kVI; ++i)
-#pragma unroll
-      for (int h = 0; h < G; ++h) acc[i][h] *= alpha[h];
-    wave_lds_sync();
-
-    // ---- p . v ----
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j) {
-      if (bid[j] < 0) continue;
-      const int tok0 = tb + j * S::kBS + vrc * S::kVec;   // first token of this lane's chunk
-      if constexpr (BF16) {
-        // 4 token pairs x G heads of bf16 pairs
-        uint32_t pw[4][G];
-        const uint4* pp = reinterpret_cast<const uint4*>(p_lds) + ((j * 8 + vrc * 4) * G) / 4;
-#pragma unroll
-        for (int x = 0; x < G; ++x) {
-          const uint4 w = pp[x];
-          const uint32_t ws4[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-          for (int y = 0; y < 4; ++y) {
-            const int idx = x * 4 + y;      // = pair * G + head
-            pw[idx / G][idx % G] = ws4[y];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < S::kVI; ++i) {
-          uint4 v = vreg[j][i];
-          if (kTail) {
-            uint32_t vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const uint32_t lo = (tok0 + 2 * k < t1) ? 0x0000ffffu : 0u;
-              const uint32_t hi = (tok0 + 2 * k + 1 < t1) ? 0xffff0000u : 0u;
-              vv[k] &= (lo | hi);
-            }
-            v = make_uint4(vv[0], vv[1], vv[2], vv[3]);
-          }
-#pragma unroll
-          for (int h = 0; h < G; ++h) {
-            float a = acc[i][h];
-            a = dot2_bf16(v.x, pw[0][h], a);
-            a = dot2_bf16(v.y, pw[1][h], a);
-            a = dot2_bf16(v.z, pw[2][h], a);
-            a = dot2_bf16(v.w, pw[3][h], a);
-            acc[i][h] = a;
-          }
-        }
-      } else {
-        float pf[4][G];
-        const float* pp = reinterpret_cast<const float*>(p_lds) + (j * S::kBS + vrc * 4) * G;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-          for (int h = 0; h < G; ++h) pf[k][h] = pp[k * G + h];
-#pragma unroll
-        for (int i = 0; i < S::kVI; ++i) {
-          const uint4 v = vreg[j][i];
-          float vf[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
-                         __uint_as_float(v.w)};
-          if (kTail) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) vf[k] = (tok0 + k < t1) ? vf[k] : 0.f;
-          }
-#pragma unroll
-          for (int h = 0; h < G; ++h) {
-            float a = acc[i][h];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a = fmaf(pf[k][h], vf[k], a);
-            acc[i][h] = a;
-          }
-        }
-      }
-    }
-    wave_lds_sync();
-  }
-
-  // ---- finish: lane sums, merge the chunks of a dim row ----
-  float l_tot[G];
-#pragma unroll
-  for (int h = 0; h < G; ++h) l_tot[h] = wave_sum(l_run[h]);
-#pragma unroll
-  for (int i = 0; i < S::kVI; ++i)
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int o = 1; o < S::kR; o <<= 1) acc[i][h] += __shfl_xor(acc[i][h], o, kWave);
-
-  // ---- merge the wavefronts' states (log-sum-exp, in context order) ----
-  __shared__ float o_lds[W][G][D];
+  __shared__ __attribute__((aligned(16))) float o_lds[W][G * D];
   __shared__ float2 ml_lds[W][G];
-  if (wave < parts) {
-    if (vrc == 0) {
-#pragma unroll
-      for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int i = 0; i < S::kVI; ++i) o_lds[wave][h][i * S::kDPI + lane / S::kR] = acc[i][h];
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) ml_lds[wave][h] = make_float2(m_run[h], l_tot[h]);
-    }
+  if constexpr (BF16) {
+    if (wave < parts)
+      walk_bf16<D, G, kTwo>(tiles, reinterpret_cast<const uint16_t*>(q_row), my_id, t0, t1,
+                            scale_log2, o_lds[wave], ml_lds[wave]);
+  } else {
+    __shared__ float p_lds[W][S::kTile * G];
+    __shared__ uint4 q_lds[G * S::kKCh];
+    for (int i = threadIdx.x; i < G * S::kKCh; i += W * kWave)
+      q_lds[i] = reinterpret_cast<const uint4*>(q_row)[i];
+    __syncthreads();
+    if (wave < parts)
+      walk_f32<D, G>(tiles, q_lds, p_lds[wave], my_id, t0, t1, scale_log2, o_lds[wave],
+                     ml_lds[wave]);
   }
   __syncthreads();
+
+  // ---- merge the wavefronts' states (log-sum-exp, in context order) ----
   for (int e = threadIdx.x; e < G * D; e += W * kWave) {
     const int h = e / D, d = e % D;
     float m = -INFINITY;
@@ -382,7 +489,7 @@ void decode_split_kernel(
       const float2 ml = ml_lds[j][h];
       const float w = fast_exp2(ml.x - ref);
       l = fmaf(w, ml.y, l);
-      o = fmaf(w, o_lds[j][h][d], o);
+      o = fmaf(w, o_lds[j][e], o);
     }
     if (nsplit == 1) {
       const float inv = l > 0.f ? 1.f / l : 0.f;

@@ -76,8 +76,6 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
   return r;
 }
 
-constexpr uint32_t kBf16OnePair = 0x3f803f80u;   // (1.0, 1.0) in bf16
-
 // Two loads of 16 bytes per lane from global memory straight into LDS
 // (global_load_lds_dwordx4): load j has lane l read base_j + off_j and its
 // bytes land at LDS byte address lds_j + 16 l (base_j and lds_j wave-uniform,
