@@ -49,6 +49,7 @@
 // them (log-sum-exp), in an order that depends only on the sequence's length.
 
 #include "common.hpp"
+#include "decode_walk.hpp"
 #include "launch.hpp"
 
 namespace kvattn {
@@ -61,211 +62,13 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int D, bool BF16>
-struct DecodeShape {
-  static constexpr int kEsz = BF16 ? 2 : 4;
-  static constexpr int kVec = 16 / kEsz;          // elements per 16-byte chunk
-  static constexpr int kBS = 16;                  // tokens per block
-  static constexpr int kTile = 64;                // tokens per wavefront step
-  static constexpr int kTB = kTile / kBS;         // blocks per step
-  static constexpr int kKCh = D / kVec;           // 16-byte chunks per K row
-  static constexpr int kR = kBS * kEsz / 16;      // 16-byte chunks per V dim row
-  static constexpr int kDPI = kWave / kR;         // V dim rows per load
-  static constexpr int kVI = D / kDPI;            // V loads per block
-  static constexpr int kTileElems = kBS * D;      // one (block, K/V, head) tile
-  static_assert(kVI * 1024 == kTileElems * kEsz, "V tile is kVI loads of 1 KiB");
-  static_assert(kKCh == 4 * kVI, "a K load of 1 KiB holds a quarter of each of 16 rows");
-};
-
-// Where a workgroup's K and V tiles lie.
-// kTwo: the layer is split over two tensors (the design the paper rejects in
-// Section 3, "The contiguity constraint"): ids below num_base address kv, the
-// others kv2 at id - num_base. Otherwise kv2 and num_base are unused.
-template <bool kTwo>
-struct DecodeTiles {
-  const uint8_t* kv;
-  const uint8_t* kv2;
-  int num_base;
-  size_t block_bytes, k_off, v_off;
-  __device__ __forceinline__ const uint8_t* block(int id) const {
-    if constexpr (kTwo)
-      return id < num_base ? kv + (size_t)id * block_bytes
-                           : kv2 + (size_t)(id - num_base) * block_bytes;
-    else
-      return kv + (size_t)id * block_bytes;
-  }
-};
-
-// The four blocks of a step: each block's K tile and V tile as they lie in
-// memory, 1 KiB per load, the two tiles of a block issued together. Within a
-// V load lane l takes 16-byte chunk v_lane of the KiB. A block without a valid
-// id (< 0) gives zeros.
-template <int kTB, int kVI, bool kTwo>
-__device__ __forceinline__ void load_step(const DecodeTiles<kTwo>& t, const int (&bid)[kTB],
-                                          int lane, int v_lane, uint4 (&kreg)[kTB][kVI],
-                                          uint4 (&vreg)[kTB][kVI]) {
-#pragma unroll
-  for (int j = 0; j < kTB; ++j) {
-    if (bid[j] >= 0) {
-      const uint8_t* bp = t.block(bid[j]);
-      const uint4* kp = reinterpret_cast<const uint4*>(bp + t.k_off) + lane;
-      const uint4* vp = reinterpret_cast<const uint4*>(bp + t.v_off) + v_lane;
-#pragma unroll
-      for (int i = 0; i < kVI; ++i) {
-        kreg[j][i] = load_nt(kp + i * kWave);
-        vreg[j][i] = load_nt(vp + i * kWave);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < kVI; ++i) {
-        kreg[j][i] = make_uint4(0, 0, 0, 0);
-        vreg[j][i] = make_uint4(0, 0, 0, 0);
-      }
-    }
-  }
-}
-
-// One wavefront's walk over tokens [t0, t1) in bf16, on the matrix units: with
-// query heads as the 16 columns (G of them real, the rest zero), a step is 16
-// products of 16 x 16 x 32 for q.k and 16 for p.v at head_dim 128, whatever G
-// is, where bf16 dot2 on the vector unit took 128 G instructions per step.
-//   S[token][head]: A = a KiB of the K tile exactly as loaded (lane l: slot
-//     l % 16, chunk 4 i + l / 16), B = q in registers. Lane l gets tokens
-//     4 (l / 16) .. + 4 of each block for head l % 16, so the softmax state is
-//     per lane and one row exchange gives the max.
-//   O^T[dim][head] += V^T P^T over 32 tokens, two blocks: the B operand needs 8
-//     consecutive tokens per lane, which one swap of the odd lane rows of the
-//     first block's P with the even rows of the second's gives; the same swap
-//     of the two blocks' V loads gives the matching A operands of 16 dims each.
-// my_id: lane l holds the id of the walk's block l (-1: none). Leaves the
-// wavefront's state in o_out [G][D] and ml_out [G] (LDS).
-template <int D, int G, bool kTwo>
-__device__ __forceinline__ void walk_bf16(const DecodeTiles<kTwo>& tiles,
-                                          const uint16_t* __restrict__ q, int my_id, int t0,
-                                          int t1, float scale_log2, float* o_out,
-                                          float2* ml_out) {
-  using S = DecodeShape<D, true>;
-  const int lane = threadIdx.x % kWave;
-  const int head = lane % 16, row = lane / 16;
-  uint4 qreg[S::kVI];
-#pragma unroll
-  for (int i = 0; i < S::kVI; ++i) {
-    qreg[i] = *reinterpret_cast<const uint4*>(q + min(head, G - 1) * D + i * 32 + row * 8);
-    if (head >= G) qreg[i] = make_uint4(0, 0, 0, 0);
-  }
-
-  float m_run = -INFINITY, l_run = 0.f;   // head's max; the lane's part of its sum
-  f32x4_t acc[2 * S::kVI];
-#pragma unroll
-  for (int i = 0; i < 2 * S::kVI; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  // lane's 16 bytes of a V KiB (32 dims x 2 halves): dim l % 32, half l / 32
-  const int v_lane = 2 * (lane % 32) + lane / 32;
-
-  for (int tb = t0; tb < t1; tb += S::kTile) {
-    const bool tail = tb + S::kTile > t1;   // the step may end inside a block
-    int bid[S::kTB];
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j)
-      bid[j] = __builtin_amdgcn_readlane(my_id, (tb - t0) / S::kBS + j);
-    uint4 kreg[S::kTB][S::kVI], vreg[S::kTB][S::kVI];
-    load_step(tiles, bid, lane, v_lane, kreg, vreg);
-
-    // ---- scores ----
-    float x[S::kTB][4];
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j) {
-      f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < S::kVI; ++i)
-        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kreg[j][i]),
-                                                     __builtin_bit_cast(bf16x8_t, qreg[i]), sc, 0,
-                                                     0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool keep = bid[j] >= 0 && (!tail || tb + j * S::kBS + row * 4 + r < t1);
-        x[j][r] = keep ? sc[r] * scale_log2 : -INFINITY;
-      }
-    }
-
-    // ---- online softmax over the step (log2 domain) ----
-    float mx = m_run;
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) mx = fmaxf(mx, x[j][r]);
-    const float mn = cross_row_max(mx);
-    const float ref = (mn == -INFINITY) ? 0.f : mn;
-    const float alpha = fast_exp2(m_run - ref);
-    m_run = mn;
-    float psum = 0.f;
-    uint2 pw[S::kTB];
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j) {
-      pw[j].x = pack_bf16x2(fast_exp2(x[j][0] - ref), fast_exp2(x[j][1] - ref));
-      pw[j].y = pack_bf16x2(fast_exp2(x[j][2] - ref), fast_exp2(x[j][3] - ref));
-      // the row sum adds the bf16 values that p.v multiplies
-      psum = dot2_bf16(pw[j].x, kBf16OnePair, psum);
-      psum = dot2_bf16(pw[j].y, kBf16OnePair, psum);
-    }
-    l_run = fmaf(l_run, alpha, psum);
-#pragma unroll
-    for (int i = 0; i < 2 * S::kVI; ++i) acc[i] *= alpha;
-
-    // ---- p . v, two blocks at a time ----
-    if (tail) {
-#pragma unroll
-      for (int j = 0; j < S::kTB; ++j) {
-        // slots at or past t1 may hold anything, and zero times NaN is NaN
-        const int tok = tb + j * S::kBS + (lane / 32) * 8;
-#pragma unroll
-        for (int i = 0; i < S::kVI; ++i) {
-          uint32_t w[4] = {vreg[j][i].x, vreg[j][i].y, vreg[j][i].z, vreg[j][i].w};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const uint32_t lo = (tok + 2 * k < t1) ? 0x0000ffffu : 0u;
-            const uint32_t hi = (tok + 2 * k + 1 < t1) ? 0xffff0000u : 0u;
-            w[k] &= (lo | hi);
-          }
-          vreg[j][i] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < S::kTB; j += 2) {
-      uint2 p0 = pw[j], p1 = pw[j + 1];
-      swap_rows16(p0.x, p1.x);
-      swap_rows16(p0.y, p1.y);
-      const bf16x8_t b = __builtin_bit_cast(bf16x8_t, make_uint4(p0.x, p0.y, p1.x, p1.y));
-#pragma unroll
-      for (int i = 0; i < S::kVI; ++i) {
-        uint4 lo = vreg[j][i], hi = vreg[j + 1][i];
-        swap_rows16(lo.x, hi.x);   // dims 32 i .. + 16 to lo, 32 i + 16 .. + 16 to hi
-        swap_rows16(lo.y, hi.y);
-        swap_rows16(lo.z, hi.z);
-        swap_rows16(lo.w, hi.w);
-        acc[2 * i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            __builtin_bit_cast(bf16x8_t, lo), b, acc[2 * i], 0, 0, 0);
-        acc[2 * i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            __builtin_bit_cast(bf16x8_t, hi), b, acc[2 * i + 1], 0, 0, 0);
-      }
-    }
-  }
-
-  const float l_tot = cross_row_sum(l_run);
-  if (head < G) {
-#pragma unroll
-    for (int i = 0; i < 2 * S::kVI; ++i)
-      *reinterpret_cast<f32x4_t*>(o_out + head * D + i * 16 + row * 4) = acc[i];
-    if (row == 0) ml_out[head] = make_float2(m_run, l_tot);
-  }
-}
-
 // The same in fp32 on the vector unit. Each lane dots its quarter of the rows
 // of the four tokens in its slot (one per block) with the same dims of q (read
 // from LDS), and the four lanes of a slot add their quarters with two row
 // swaps; lane t then takes the score of token t of the step. In the dim-major V
 // tile lane l owns dim rows l / R (R = 16-byte chunks per row) and a run of
-// consecutive tokens, whose p reach it through LDS.
+// consecutive tokens, whose p reach it through LDS. my_id: the ids of the walk's
+// blocks (at most 64), one per lane.
 template <int D, int G>
 __device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const uint4* q_lds,
                                          float* p_lds, int my_id, int t0, int t1,
@@ -421,7 +224,6 @@ void decode_split_kernel(
   const int g = wid % num_kv_heads;
   const int s = (wid / num_kv_heads) % num_seqs;
   const int split = wid / (num_kv_heads * num_seqs);
-  const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int h0 = g * G;
   const size_t row_bytes = (size_t)D * S::kEsz;
@@ -447,12 +249,7 @@ void decode_split_kernel(
   const int t0 = s0 + wave * part_tokens;                    // this wavefront's tokens
   const int t1 = min(s1, t0 + part_tokens);
 
-  // The ids of the wavefront's blocks, one per lane (a split has at most 64
-  // blocks): one load instead of one dependent load per step.
   const int* bt = block_table + (size_t)s * max_blocks;
-  int my_id = -1;
-  if (t0 + lane * S::kBS < t1) my_id = bt[t0 / S::kBS + lane];
-  if ((unsigned)my_id >= (unsigned)num_blocks) my_id = -1;
 
   const size_t tile_bytes = (size_t)S::kTileElems * S::kEsz;
   const size_t head_off = (size_t)g * tile_bytes;
@@ -464,8 +261,8 @@ void decode_split_kernel(
   __shared__ float2 ml_lds[W][G];
   if constexpr (BF16) {
     if (wave < parts)
-      walk_bf16<D, G, kTwo>(tiles, reinterpret_cast<const uint16_t*>(q_row), my_id, t0, t1,
-                            scale_log2, o_lds[wave], ml_lds[wave]);
+      walk_bf16<D, G, kTwo>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt, num_blocks, t0,
+                            t1, scale_log2, o_lds[wave], ml_lds[wave]);
   } else {
     __shared__ float p_lds[W][S::kTile * G];
     __shared__ uint4 q_lds[G * S::kKCh];
@@ -473,8 +270,8 @@ void decode_split_kernel(
       q_lds[i] = reinterpret_cast<const uint4*>(q_row)[i];
     __syncthreads();
     if (wave < parts)
-      walk_f32<D, G>(tiles, q_lds, p_lds[wave], my_id, t0, t1, scale_log2, o_lds[wave],
-                     ml_lds[wave]);
+      walk_f32<D, G>(tiles, q_lds, p_lds[wave], walk_ids(bt, t0, t1, num_blocks), t0, t1,
+                     scale_log2, o_lds[wave], ml_lds[wave]);
   }
   __syncthreads();
 
