@@ -170,10 +170,19 @@ const char* kvattn_trace_kernel_name(int i);
  * max_num_batched_tokens  the step's token budget: total_q_tokens must not
  *               exceed it (KV_ERR_INVALID otherwise); it sizes no buffer and
  *               never changes the arithmetic
- * workspace     device scratch of kvattn_prefill_workspace_bytes(...) bytes
+ * workspace     device scratch of kvattn_prefill_workspace_bytes(...) bytes, no
+ *               initial contents needed, not used by another call in flight.
+ *               About 65 MiB of it hold partial results of work tiles whose
+ *               keys several workgroups share, which is how a call with few
+ *               tiles fills the chip; a workspace of only
+ *               align256(8 * (total_q_tokens / 32 + num_seqs + 1) + 16) bytes
+ *               is accepted too and every tile is then one workgroup's
  *
  * Causal alignment is bottom-right: row i of sequence s sees keys
- * 0 .. seq_lens[s] - n_s + i. Supported: bf16, block_size 16, head_dim 128,
+ * 0 .. seq_lens[s] - n_s + i. Whether a tile's keys are shared depends on the
+ * whole call (its sequences, chunk sizes and lengths), so the last bits of a row
+ * can differ between calls that batch it differently; calls of four or more
+ * tiles per CU never share. Supported: bf16, block_size 16, head_dim 128,
  * num_q_heads / num_kv_heads in {1, 2, 4, 8}; KV_F32 returns KV_ERR_UNSUPPORTED.
  * Asynchronous; allocates nothing.
  */

@@ -288,12 +288,19 @@ int decode_launch(const char* fn, const kvattn::DecodeArgs& a) {
 
 }  // namespace
 
+namespace {
+// The least a prefill call takes: the list of whole work tiles, one int2 per
+// tile of kPrefillRows query rows of a sequence.
+size_t prefill_min_bytes(int num_seqs, int total_q_tokens) {
+  const size_t tiles = (size_t)total_q_tokens / kvattn::kPrefillRows + num_seqs + 1;
+  return align256(tiles * 2 * sizeof(int32_t) + 16);
+}
+}  // namespace
+
 extern "C" size_t kvattn_prefill_workspace_bytes(int num_seqs, int total_q_tokens,
                                                  int num_q_heads, int head_dim) {
   if (num_seqs < 0 || total_q_tokens < 0 || num_q_heads <= 0 || head_dim <= 0) return 0;
-  // Work-tile list: one int2 per tile of kPrefillRows query rows of a sequence.
-  const size_t tiles = (size_t)total_q_tokens / kvattn::kPrefillRows + num_seqs + 1;
-  return align256(tiles * 2 * sizeof(int32_t) + 16);
+  return align256(kvattn::prefill_planned_bytes(num_seqs, total_q_tokens));
 }
 
 extern "C" int kvattn_prefill_chunk(const void* q, const void* kv_layer, int num_blocks,
@@ -343,8 +350,7 @@ extern "C" int kvattn_prefill_chunk(const void* q, const void* kv_layer, int num
   if (!aligned16(q) || !aligned16(kv_layer) || !aligned16(out) || !aligned16(workspace))
     return set_error(KV_ERR_INVALID, "kvattn_prefill_chunk: q, kv_layer, out and workspace "
                                      "must be 16-byte aligned");
-  const size_t need = kvattn_prefill_workspace_bytes(num_seqs, total_q_tokens, num_q_heads,
-                                                     head_dim);
+  const size_t need = prefill_min_bytes(num_seqs, total_q_tokens);
   if (workspace_bytes < need)
     return set_error(KV_ERR_INVALID, "kvattn_prefill_chunk: workspace %zu bytes < %zu needed",
                      workspace_bytes, need);

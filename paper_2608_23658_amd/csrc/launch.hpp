@@ -79,4 +79,7 @@ hipError_t launch_copy_blocks(const CopyArgs& a);
 // size 8; the workspace's tile list is sized for it.
 constexpr int kPrefillRows = 32;
 
+// Workspace of a planned prefill step, whatever its head counts.
+size_t prefill_planned_bytes(int num_seqs, int total_q_tokens);
+
 }  // namespace kvattn

@@ -60,6 +60,7 @@ constexpr int kKBufs = 3;                  // LDS K steps (gathered three steps 
 constexpr int kVBufs = 3;                  // LDS V steps (gathered one step ahead)
 constexpr int kWaves = 8;                  // wavefronts per workgroup
 constexpr int kThreads = kWaves * kWave;
+constexpr int kNumCUs = 256;               // gfx950
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
@@ -188,6 +189,357 @@ __global__ __launch_bounds__(256) void prefill_tile_map_kernel(const int* __rest
   if (tid == 255) *count = min(scan[255], max_tiles);
 }
 
+// ---- planned steps ----
+//
+// With the workspace kvattn_prefill_workspace_bytes asks for, a step's work is
+// laid out by a plan kernel. An item is a run of key steps of one work tile
+// (for all kv heads); a tile whose keys are shared by several items leaves a
+// partial state per item in a slot, and prefill_combine_kernel merges them.
+// A tile is a serial walk of about 1.7 us per key step, one workgroup per CU,
+// so a step with few tiles leaves CUs idle, and one whose tiles do not divide
+// by the CUs idles them in its last round. A call at 32 query heads over 8,
+// whole tiles in sequence order against planned items:
+//   201 rows over 6150 cached tokens (32 workgroups of 100 steps)  162 -> 44 us
+//   512 rows over 8192                                             215 -> 88 us
+//   1024 rows over 1024                                             62 -> 53 us
+//   9 chunks of 100 to 900 rows over 1000 to 8000 tokens           443 -> 367 us
+//   8192 rows over 24576 (four even rounds, not shared)           3274, 3278 us
+
+struct PrefillItem {
+  int s, q0;        // sequence, first row of the tile in the chunk
+  int i0, i1;       // key steps, i0 even
+  int slot;         // partial slot, -1: the whole tile, written to out
+  int cu0, n, L;    // the sequence's chunk and clamped length
+};
+
+struct PrefillSplit {   // a tile shared by several items
+  int row0, rows;       // its rows in q and out
+  int slot0, pieces;
+};
+
+struct PrefillPlan {
+  int items, splits;
+  int pad[2];
+};
+
+// A slot holds, for each of the 8 wavefronts of a tile and its 32 rows, O
+// unnormalised in fp32 as [dim pair][row] and (reference max, row sum).
+constexpr int kSlotFloats = kWaves * 32 * kD;
+constexpr size_t kSlotBytes = kSlotFloats * sizeof(float) + kWaves * 32 * sizeof(float2);
+
+constexpr int kPlanThreads = 512;
+constexpr int kPlanCandidates = 16;
+// Estimated cost, in key steps, of an item's prologue and epilogue, and of
+// writing and merging a partial.
+constexpr int kItemSteps = 3, kPartialSteps = 6;
+constexpr int kCombineParts = 4;   // workgroups over the dims of a merge
+constexpr int kCombineGrid = 1024;
+
+struct PlanArgs {
+  const int* cu;
+  const int* seq_lens;
+  int num_seqs, total_q, rows_per_tile, num_kv_heads, max_seq_tokens;
+  int max_items, max_slots;   // max_slots 0: no tile is shared
+  PrefillItem* items;
+  PrefillSplit* splits;
+  PrefillPlan* head;
+};
+
+// Steps per item and items of a tile of N steps, at most C steps per item.
+__device__ __forceinline__ int2 tile_pieces(int N, int C) {
+  const int p = (N + C - 1) / C;
+  if (p <= 1) return make_int2(N, 1);
+  const int per = (((N + p - 1) / p) + 1) & ~1;   // whole pairs of steps
+  return make_int2(per, (N + per - 1) / per);
+}
+
+// Exclusive prefix sum over the workgroup; *total gets the sum.
+__device__ __forceinline__ int plan_scan(int v, int* lds, int* total) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int y = __shfl_up(x, o, kWave);
+    x += lane >= o ? y : 0;
+  }
+  if (lane == kWave - 1) lds[wave] = x;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kPlanThreads / kWave; ++w) {
+    before += w < wave ? lds[w] : 0;
+    all += lds[w];
+  }
+  __syncthreads();
+  *total = all;
+  return before + x - v;
+}
+
+// Tile t of a chunk of sequences: its sequence's index in the chunk, first row,
+// key steps.
+struct PlanTile {
+  int idx, q0, N;
+};
+
+// Latency-bound, one workgroup ahead of the attention kernel. While the
+// sequences fit one chunk (512) and their tiles one per thread, the usual case,
+// each thread keeps its tile in registers over all passes: 5.0 us (6.6 with
+// candidates to weigh) where finding the tiles again in each pass and one
+// thread weighing the candidates took 10.3 and 15.1; the tile map takes 4.7.
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) {
+  __shared__ int seq_cu[kPlanThreads], seq_n[kPlanThreads], seq_L[kPlanThreads];
+  __shared__ int first[kPlanThreads + 1];     // first tile of each sequence of the chunk
+  __shared__ int scan_lds[kPlanThreads / kWave];
+  __shared__ int hist[256], steps[kPlanThreads];
+  __shared__ unsigned long long sum_steps;
+  __shared__ int max_steps, best_c, next_slot, next_split;
+  __shared__ int cand_items[kPlanCandidates], cand_slots[kPlanCandidates];
+  const int tid = threadIdx.x;
+  const int R = a.rows_per_tile;
+  const int seqs = min(a.num_seqs, kPlanThreads);   // sequences of a chunk, at most
+
+  // Loads sequences base .. base + 511 and numbers their tiles.
+  auto load_chunk = [&](int base) {
+    const int s = base + tid;
+    int nt = 0;
+    if (s < a.num_seqs) {
+      const int len = a.seq_lens[s];
+      const int2 r = chunk_rows(a.cu, s, a.total_q);
+      seq_cu[tid] = r.x;
+      seq_n[tid] = r.y - r.x;
+      seq_L[tid] = min(max(len, 0), a.max_seq_tokens);
+      nt = (r.y - r.x + R - 1) / R;
+    }
+    int total;
+    const int at = plan_scan(nt, scan_lds, &total);
+    first[tid] = at;
+    if (tid == 0) first[kPlanThreads] = total;
+    __syncthreads();
+    return total;
+  };
+  // The rows of a sequence are taken in descending order.
+  auto tile_of = [&](int t) {
+    int lo = 0, hi = seqs - 1;   // last sequence with first <= t, which has tiles
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) / 2;
+      if (first[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+    PlanTile r;
+    const int nt = (lo + 1 < kPlanThreads ? first[lo + 1] : first[kPlanThreads]) - first[lo];
+    const int n = seq_n[lo], L = seq_L[lo];
+    r.idx = lo;
+    r.q0 = (nt - 1 - (t - first[lo])) * R;
+    const int last_pos = min(L - n + r.q0 + min(R, n - r.q0) - 1, L - 1);
+    r.N = last_pos >= 0 ? last_pos / kKeys + 1 : 0;
+    return r;
+  };
+
+  if (tid == 0) { sum_steps = 0; max_steps = 1; next_slot = 0; next_split = 0; }
+  if (tid < 256) hist[tid] = 0;
+  int chunk_tiles = load_chunk(0);   // its barriers also publish the zeros above
+  const bool one_chunk = a.num_seqs <= kPlanThreads;
+  const bool resident = one_chunk && chunk_tiles <= kPlanThreads;   // a tile per thread
+  PlanTile own = {0, 0, 0};
+  if (resident) {
+    if (tid < chunk_tiles) own = tile_of(tid);
+    steps[tid] = own.N;
+  }
+  // Runs f(base, tile) over every tile, tiles dealt to the threads in turn.
+  auto each_tile = [&](auto f) {
+    if (resident) {
+      if (tid < chunk_tiles) f(0, own);
+      return;
+    }
+    for (int base = 0; base < a.num_seqs; base += kPlanThreads) {
+      if (!one_chunk) chunk_tiles = load_chunk(base);
+      for (int t = tid; t < chunk_tiles; t += kPlanThreads) f(base, tile_of(t));
+      __syncthreads();
+    }
+  };
+
+  // ---- totals ----
+  {
+    int tiles_seen = 0, mx = 0;
+    unsigned long long st = 0;
+    each_tile([&](int, const PlanTile& t) {
+      st += t.N;
+      mx = max(mx, t.N);
+      ++tiles_seen;
+    });
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      st += __shfl_xor(st, o, kWave);
+      mx = max(mx, __shfl_xor(mx, o, kWave));
+      tiles_seen += __shfl_xor(tiles_seen, o, kWave);
+    }
+    if (tid % kWave == 0) {
+      atomicAdd(&sum_steps, st + ((unsigned long long)tiles_seen << 40));
+      atomicMax(&max_steps, mx);
+    }
+  }
+  __syncthreads();
+  const int tiles = (int)(sum_steps >> 40), longest = max_steps;
+  const float work_steps = (float)(sum_steps & ((1ull << 40) - 1));
+  // tiles (of all kv heads) that run at once, one workgroup per CU
+  const int lanes = max(1, kNumCUs / a.num_kv_heads);
+  constexpr int kWhole = 1 << 30;
+
+  // ---- how many steps an item gets ----
+  // Candidate k limits an item to 1 / (k + 1) of the longest tile. The time of
+  // each is estimated as the larger of the whole work over the chip and the
+  // rounds its items take; the fewest items within 3% of the best win. A step
+  // with four or more rounds of tiles gains nothing and is not tried.
+  int C = kWhole;
+  if (a.max_slots > 0 && resident && tiles < 4 * lanes) {
+    constexpr int kPer = kPlanThreads / kPlanCandidates;   // 32 lanes per candidate
+    auto limit = [&](int k) { return k ? max(4, ((longest + k) / (k + 1) + 1) & ~1) : kWhole; };
+    const int cand = tid / kPer, mine = limit(cand);
+    int items = 0, slots = 0;
+    for (int t = tid % kPer; t < tiles; t += kPer) {
+      const int p = tile_pieces(steps[t], mine).y;
+      items += p;
+      slots += p > 1 ? p : 0;
+    }
+#pragma unroll
+    for (int o = kPer / 2; o > 0; o >>= 1) {
+      items += __shfl_xor(items, o, kPer);
+      slots += __shfl_xor(slots, o, kPer);
+    }
+    if (tid % kPer == 0) { cand_items[cand] = items; cand_slots[cand] = slots; }
+    __syncthreads();
+    if (tid < kPlanCandidates) {
+      const int n = cand_items[tid], k = cand_slots[tid];
+      const float work = work_steps + (float)kItemSteps * n + (float)kPartialSteps * k;
+      const float est = k > a.max_slots || n == 0
+                            ? INFINITY
+                            : fmaxf(work / lanes, ((n + lanes - 1) / lanes) * (work / n));
+      float best = est;
+#pragma unroll
+      for (int o = kPlanCandidates / 2; o > 0; o >>= 1)
+        best = fminf(best, __shfl_xor(best, o, kPlanCandidates));
+      const unsigned long long good = __ballot(est <= 1.03f * best);
+      if (tid == 0) best_c = limit(__ffsll(good) - 1);
+    }
+    __syncthreads();
+    C = best_c;
+  }
+  const float per_bucket = 255.f / max(1, min(longest, C));   // C bounds an item's steps
+
+  // ---- items in descending length, so that the last to start are short ----
+  auto bucket = [&](int per) { return 255 - min(255, (int)(per * per_bucket)); };
+  each_tile([&](int, const PlanTile& t) {
+    const int2 p = tile_pieces(t.N, C);
+    atomicAdd(&hist[bucket(p.x)], p.y);
+  });
+  __syncthreads();
+  int total;
+  const int mine = tid < 256 ? hist[tid] : 0;
+  const int at = plan_scan(mine, scan_lds, &total);
+  if (tid < 256) hist[tid] = at;
+  __syncthreads();
+  each_tile([&](int base, const PlanTile& t) {
+    const int2 p = tile_pieces(t.N, C);
+    const int j0 = atomicAdd(&hist[bucket(p.x)], p.y);
+    const int cu0 = seq_cu[t.idx], n = seq_n[t.idx], L = seq_L[t.idx];
+    int slot = -1;
+    if (p.y > 1) {
+      slot = atomicAdd(&next_slot, p.y);
+      const int k = atomicAdd(&next_split, 1);
+      a.splits[k] = {cu0 + t.q0, min(R, n - t.q0), slot, p.y};
+    }
+    for (int k = 0; k < p.y; ++k)
+      if (j0 + k < a.max_items)
+        a.items[j0 + k] = {base + t.idx, t.q0, k * p.x, min(t.N, (k + 1) * p.x),
+                           slot < 0 ? -1 : slot + k, cu0, n, L};
+  });
+  __syncthreads();
+  if (tid == 0) *a.head = {min(total, a.max_items), next_split, {0, 0}};
+}
+
+// Merge the partials of the shared tiles: one workgroup per (tile, kv head,
+// wavefront of the tile's 8, quarter of the dims), 32 rows of one query head.
+// Bound by the latency of reading the partials, 4 KiB each: every load is a
+// row's 8 bytes per lane, contiguous over the rows, and four partials' loads are
+// issued together; the merged rows go through LDS to be written in 64-byte
+// pieces. 7 us for 28 tiles' heads of 8 partials (26 MB); one workgroup per 32
+// rows of all dims, a partial at a time, took 8.5.
+template <int G>
+__global__ __launch_bounds__(256) void prefill_combine_kernel(
+    const PrefillPlan* __restrict__ head, const PrefillSplit* __restrict__ splits,
+    const uint8_t* __restrict__ slots, uint16_t* __restrict__ out, int num_q_heads,
+    int num_kv_heads) {
+  constexpr int kPart = kCombineParts;
+  __shared__ uint32_t tile[32][kD / 2 / kPart + 1];
+  const int tasks = head->splits * num_kv_heads * kWaves * kPart;
+  for (int task = blockIdx.x; task < tasks; task += gridDim.x) {
+    const int part = task % kPart;
+    const int w = (task / kPart) % kWaves;
+    const int g = (task / (kPart * kWaves)) % num_kv_heads;
+    const PrefillSplit sp = splits[task / (kPart * kWaves * num_kv_heads)];
+    const int r0 = (w / G) * 32;
+    if (r0 >= sp.rows) continue;
+    constexpr int kDimPairs = kD / 2 / kPart;          // of this workgroup
+    constexpr int kPer = kDimPairs / 8;                // of a thread: p0 + 8 i
+    constexpr int kBatch = 4;
+    const int row = threadIdx.x % 32, p0 = threadIdx.x / 32;
+    const size_t stride = (size_t)num_kv_heads * kSlotBytes;
+    const uint8_t* base = slots + ((size_t)sp.slot0 * num_kv_heads + g) * kSlotBytes;
+    const uint8_t* ml_base = base + (size_t)kSlotFloats * sizeof(float) +
+                             (w * 32 + row) * sizeof(float2);
+    const uint8_t* o_base = base + ((w * (kD / 2) + part * kDimPairs + p0) * 32 + row) *
+                                       sizeof(float2);
+
+    float m = -INFINITY, l = 0.f;
+    float2 o[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) o[i] = make_float2(0.f, 0.f);
+    for (int j0 = 0; j0 < sp.pieces; j0 += kBatch) {
+      float2 ml[kBatch], v[kBatch][kPer];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) {   // past the end: the last partial, at weight 0
+        const size_t at = (size_t)min(j0 + b, sp.pieces - 1) * stride;
+        ml[b] = *reinterpret_cast<const float2*>(ml_base + at);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+          v[b][i] = *reinterpret_cast<const float2*>(o_base + at + i * 8 * 32 * sizeof(float2));
+      }
+      float mn = m;
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) mn = fmaxf(mn, ml[b].x);
+      const float ref = (mn == -INFINITY) ? 0.f : mn;
+      const float alpha = fast_exp2(m - ref);
+      m = mn;
+      l *= alpha;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) { o[i].x *= alpha; o[i].y *= alpha; }
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) {
+        if (j0 + b >= sp.pieces) break;
+        const float wgt = fast_exp2(ml[b].x - ref);
+        l = fmaf(wgt, ml[b].y, l);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+          o[i].x = fmaf(wgt, v[b][i].x, o[i].x);
+          o[i].y = fmaf(wgt, v[b][i].y, o[i].y);
+        }
+      }
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      tile[row][p0 + 8 * i] = pack_bf16x2(o[i].x * inv, o[i].y * inv);
+    __syncthreads();
+    const int nrows = min(32, sp.rows - r0);
+    const int h = g * G + w % G;
+    for (int e = threadIdx.x; e < nrows * kDimPairs; e += 256) {
+      const int r = e / kDimPairs, d2 = e % kDimPairs;
+      reinterpret_cast<uint32_t*>(out)[((size_t)(sp.row0 + r0 + r) * num_q_heads + h) * (kD / 2) +
+                                       part * kDimPairs + d2] = tile[r][d2];
+    }
+    __syncthreads();   // the next task writes the tile
+  }
+}
+
 template <int G, bool kPow2Blocks>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
                           amdgpu_waves_per_eu(2, 2)))
@@ -195,31 +547,39 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ 
                     int num_blocks, const int* __restrict__ block_table,
                     const int* __restrict__ seq_lens, const int* __restrict__ cu,
                     uint16_t* __restrict__ out, const int2* __restrict__ tiles,
-                    const int* __restrict__ tile_count, int total_q, int num_q_heads,
-                    int num_kv_heads,
+                    const int* __restrict__ tile_count, const PrefillItem* __restrict__ items,
+                    uint8_t* __restrict__ slots, int total_q, int num_q_heads, int num_kv_heads,
                     int max_blocks, int max_seq_len, float scale_log2) {
   constexpr int kRows = 32 * kWaves / G;   // rows per work tile
   const int wid = blockIdx.x;
   const int g = wid % num_kv_heads;
   const int ti = wid / num_kv_heads;
+  PrefillItem it;
+  if (items) it = items[ti];   // the list has room for the whole grid: read beside the count
   if (ti >= *tile_count) return;
-  const int2 tl = tiles[ti];
-  const int s = tl.x;
-  const int q0 = tl.y;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // uniform per wavefront
   const int lane = tid % kWave;
   const int h = g * G + wave % G;
+  if (!items) {   // no plan: the tile map's whole tiles
+    const int2 tl = tiles[ti];
+    const int2 rows = chunk_rows(cu, tl.x, total_q);
+    it.s = tl.x;
+    it.q0 = tl.y;
+    it.cu0 = rows.x;
+    it.n = rows.y - rows.x;
+    it.L = min(max(seq_lens[tl.x], 0), min(max_seq_len, max_blocks * kBS));
+    const int last_pos = min(it.L - it.n + it.q0 + min(kRows, it.n - it.q0) - 1, it.L - 1);
+    it.i0 = 0;
+    it.i1 = last_pos >= 0 ? last_pos / kKeys + 1 : 0;
+    it.slot = -1;
+  }
+  const int s = it.s, q0 = it.q0, cu0 = it.cu0, n = it.n;
+  const int L = __builtin_amdgcn_readfirstlane(it.L);
   const int row0 = q0 + (wave / G) * 32;        // first row of this wave
-  const int2 rows = chunk_rows(cu, s, total_q);
-  const int cu0 = rows.x;
-  const int n = rows.y - rows.x;
-  int L = seq_lens[s];
-  L = __builtin_amdgcn_readfirstlane(min(max(L, 0), min(max_seq_len, max_blocks * kBS)));
   const int c = L - n;                          // cached context before the chunk
-  const int wg_rows = min(kRows, n - q0);
-  const int last_pos = min(c + q0 + wg_rows - 1, L - 1);
-  const int N = last_pos >= 0 ? last_pos / kKeys + 1 : 0;   // steps of the tile
+  const int i0 = it.i0, N = it.i1;              // steps of the item
+  __builtin_assume(i0 >= 0 && N >= 0);
   const bool idle = row0 >= n;                  // none of the wave's 32 rows is in the chunk
 
   __shared__ __attribute__((aligned(16))) uint8_t lds_k[kKBufs][kStepBlocks][kTileBytes];
@@ -602,15 +962,15 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ 
   // of every gather and meets every barrier, step for step like the others,
   // but does no matrix or softmax work and writes nothing.
   if (idle) {
-    if (N > 0) {
-      load_half(std::false_type{}, 0);
-      if (N > 1) load_half(std::false_type{}, 1);
-      if (N > 2) load_half(std::false_type{}, 2);
-      load_half(std::true_type{}, 0);
+    if (N > i0) {
+      load_half(std::false_type{}, i0);
+      if (i0 + 1 < N) load_half(std::false_type{}, i0 + 1);
+      if (i0 + 2 < N) load_half(std::false_type{}, i0 + 2);
+      load_half(std::true_type{}, i0);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      __syncthreads();   // the others' q.k of step 0
-      for (int i = 0; i < N; ++i) {
+      __syncthreads();   // the others' q.k of the first step
+      for (int i = i0; i < N; ++i) {
         if (i + 3 < N) load_half(std::false_type{}, i + 3);
         if (i + 1 < N) load_half(std::true_type{}, i + 1);
         if (i + 3 < N)
@@ -625,24 +985,24 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ 
     return;
   }
 
-  if (N > 0) {
-    bits0 = load_half(std::false_type{}, 0);
-    if (N > 1) bits1 = load_half(std::false_type{}, 1);
-    if (N > 2) bits2 = load_half(std::false_type{}, 2);
-    load_half(std::true_type{}, 0);
-    if (N > 3) idsK = step_ids(3);
-    if (N > 1) idsV = step_ids(1);
+  if (N > i0) {
+    bits0 = load_half(std::false_type{}, i0);
+    if (i0 + 1 < N) bits1 = load_half(std::false_type{}, i0 + 1);
+    if (i0 + 2 < N) bits2 = load_half(std::false_type{}, i0 + 2);
+    load_half(std::true_type{}, i0);
+    if (i0 + 3 < N) idsK = step_ids(i0 + 3);
+    if (i0 + 1 < N) idsV = step_ids(i0 + 1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    qk(0, sA);
-    __syncthreads();   // K of step 0 is read; step 0 of the pipeline gathers step 3 into its buffer
+    qk(i0, sA);
+    __syncthreads();   // K of the first step is read; its pipeline step gathers into its buffer
     constexpr std::true_type T{};
     constexpr std::false_type F{};
-    if (N > 1)
-      phase(T, F, 0, sA, sB, pB, pA);
+    if (i0 + 1 < N)
+      phase(T, F, i0, sA, sB, pB, pA);
     else
-      phase(F, F, 0, sA, sB, pB, pA);
-    int i = 1;
+      phase(F, F, i0, sA, sB, pB, pA);
+    int i = i0 + 1;   // i0 is even: even steps use sA and pA
     for (; i + 1 <= N - 2; i += 2) {
       phase(T, T, i, sB, sA, pA, pB);
       phase(T, T, i + 1, sA, sB, pB, pA);
@@ -652,7 +1012,7 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ 
       ++i;
     }
     // p.v of the last step (its V landed by the last step's full wait)
-    if (N > 1) {
+    if (i0 + 1 < N) {
       if (i & 1)
         phase(F, T, i, sB, sA, pA, pB);
       else
@@ -662,12 +1022,12 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ 
     pv(N - 1, ((N - 1) & 1) ? pB : pA);
   }
 
-  // ---- normalise and write O (this lane: row lm) ----
+  // ---- write O (this lane: row lm): normalised, or the item's partial ----
   {
     const float lt = l_run + __shfl_xor(l_run, 32, kWave);
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;
     const int r = row0 + lm;
-    if (r < n) {
+    if (r < n && it.slot < 0) {
+      const float inv = lt > 0.f ? 1.f / lt : 0.f;
       uint16_t* orow = out + (size_t)(cu0 + r) * qstride + (size_t)h * kD;
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) {
@@ -679,26 +1039,108 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ 
           *reinterpret_cast<uint2*>(orow + dt * 32 + a * 8 + lh * 4) = w;
         }
       }
+    } else if (r < n) {
+      uint8_t* slot = slots + ((size_t)it.slot * num_kv_heads + g) * kSlotBytes;
+      float2* po = reinterpret_cast<float2*>(slot) + wave * 32 * (kD / 2) + lm;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 8; ++a)   // dims dt 32 + (a / 2) 8 + lh 4 + (a % 2) 2 .. + 2
+          po[(dt * 16 + (a / 2) * 4 + lh * 2 + a % 2) * 32] =
+              make_float2(oacc[dt][2 * a], oacc[dt][2 * a + 1]);
+      if (lh == 0)
+        reinterpret_cast<float2*>(slot + kSlotFloats * sizeof(float))[wave * 32 + lm] =
+            make_float2(m_ref, lt);
     }
   }
+}
+
+// Offsets of a planned step's pieces of the workspace.
+namespace {
+struct PrefillWs {
+  int max_items, max_slots;     // items; slots per kv head
+  size_t items, splits, slots;  // byte offsets; the plan's head is at 0
+  size_t total;
+};
+
+size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Workgroups' worth of partial slots: the plan fills the chip once or twice.
+constexpr int kSlotWorkgroups = 2 * kNumCUs;
+
+PrefillWs prefill_ws(int num_seqs, int total_q, int rows_per_tile, int num_kv_heads) {
+  PrefillWs w;
+  w.max_slots = num_kv_heads <= kNumCUs ? kSlotWorkgroups / num_kv_heads : 0;
+  w.max_items = total_q / rows_per_tile + num_seqs + w.max_slots;
+  w.items = 256;
+  w.splits = w.items + up256((size_t)w.max_items * sizeof(PrefillItem));
+  w.slots = w.splits + up256((size_t)(w.max_slots / 2 + 1) * sizeof(PrefillSplit));
+  w.total = w.slots + (size_t)w.max_slots * num_kv_heads * kSlotBytes;
+  return w;
+}
+}  // namespace
+
+size_t prefill_planned_bytes(int num_seqs, int total_q) {
+  // the kv heads are not known here: the most items and slots any count needs
+  const size_t items = (size_t)total_q / kPrefillRows + num_seqs + kSlotWorkgroups;
+  return 256 + up256(items * sizeof(PrefillItem)) +
+         up256((kSlotWorkgroups / 2 + 1) * sizeof(PrefillSplit)) + kSlotWorkgroups * kSlotBytes;
 }
 
 template <int G>
 static hipError_t launch_prefill_t(const PrefillArgs& a) {
   constexpr int kRowsPerTile = 32 * kWaves / G;
-  int* count = reinterpret_cast<int*>(a.workspace);
-  int2* tiles = reinterpret_cast<int2*>(static_cast<uint8_t*>(a.workspace) + 16);
-  const int max_tiles =
-      static_cast<int>((a.workspace_bytes - 16) / sizeof(int2));
+  uint8_t* ws = static_cast<uint8_t*>(a.workspace);
+  const PrefillWs w = prefill_ws(a.num_seqs, a.total_q_tokens, kRowsPerTile, a.num_kv_heads);
+  // Sharing tiles needs more than 8 key steps somewhere (below that an item's
+  // own cost outweighs what it saves) and fewer than four rounds of tiles. One
+  // sequence whose tiles are not shared needs no plan either: the tile map, 1 us
+  // faster, lists its tiles in the same order.
+  const bool share = a.max_seq_len > 8 * kKeys &&
+                     (long long)(a.total_q_tokens / kRowsPerTile) * a.num_kv_heads < 4 * kNumCUs;
+  const bool planned = a.workspace_bytes >= w.total && (a.num_seqs > 1 || share);
   const long long bound = (long long)a.total_q_tokens / kRowsPerTile + a.num_seqs;
-  const int grid_tiles = (int)(bound < max_tiles ? bound : max_tiles);
-  trace_before(a.stream, "prefill_tile_map");
-  hipLaunchKernelGGL(prefill_tile_map_kernel, dim3(1), dim3(256), 0, a.stream, a.cu_seqlens_q,
-                     a.num_seqs, a.total_q_tokens, kRowsPerTile, tiles, count, grid_tiles);
+  const int2* tiles = nullptr;
+  const int* count;
+  const PrefillItem* items = nullptr;
+  int grid_items, max_slots = 0;
+  hipError_t e;
+  if (planned) {
+    max_slots = share ? w.max_slots : 0;
+    PlanArgs p;
+    p.cu = a.cu_seqlens_q;
+    p.seq_lens = a.seq_lens;
+    p.num_seqs = a.num_seqs;
+    p.total_q = a.total_q_tokens;
+    p.rows_per_tile = kRowsPerTile;
+    p.num_kv_heads = a.num_kv_heads;
+    p.max_seq_tokens = a.max_seq_len < a.max_blocks * kBS ? a.max_seq_len : a.max_blocks * kBS;
+    grid_items = (int)(bound + max_slots);
+    p.max_items = grid_items;
+    p.max_slots = max_slots;
+    p.items = reinterpret_cast<PrefillItem*>(ws + w.items);
+    p.splits = reinterpret_cast<PrefillSplit*>(ws + w.splits);
+    p.head = reinterpret_cast<PrefillPlan*>(ws);
+    items = p.items;
+    count = &p.head->items;
+    trace_before(a.stream, "prefill_plan");
+    hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, a.stream, p);
+  } else {
+    // One sequence of whole tiles, or a workspace of the tile list's size alone.
+    int* c = reinterpret_cast<int*>(ws);
+    int2* t = reinterpret_cast<int2*>(ws + 16);
+    const long long max_tiles = (long long)((a.workspace_bytes - 16) / sizeof(int2));
+    grid_items = (int)(bound < max_tiles ? bound : max_tiles);
+    tiles = t;
+    count = c;
+    trace_before(a.stream, "prefill_tile_map");
+    hipLaunchKernelGGL(prefill_tile_map_kernel, dim3(1), dim3(256), 0, a.stream, a.cu_seqlens_q,
+                       a.num_seqs, a.total_q_tokens, kRowsPerTile, t, c, grid_items);
+  }
   trace_after(a.stream);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long long blocks = (long long)grid_tiles * a.num_kv_heads;
+  const long long blocks = (long long)grid_items * a.num_kv_heads;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   trace_before(a.stream, "prefill");
@@ -707,9 +1149,18 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, a.stream,
                      static_cast<const uint16_t*>(a.q), static_cast<const uint8_t*>(a.kv),
                      a.num_blocks, a.block_table, a.seq_lens, a.cu_seqlens_q,
-                     static_cast<uint16_t*>(a.out), tiles, count, a.total_q_tokens,
-                     a.num_q_heads, a.num_kv_heads, a.max_blocks, a.max_seq_len,
-                     a.scale * kLog2e);
+                     static_cast<uint16_t*>(a.out), tiles, count, items, ws + w.slots,
+                     a.total_q_tokens, a.num_q_heads, a.num_kv_heads, a.max_blocks,
+                     a.max_seq_len, a.scale * kLog2e);
+  trace_after(a.stream);
+  e = hipGetLastError();
+  if (e != hipSuccess || max_slots == 0) return e;
+  trace_before(a.stream, "prefill_combine");
+  hipLaunchKernelGGL((prefill_combine_kernel<G>),
+                     dim3(kCombineGrid), dim3(256), 0,
+                     a.stream, reinterpret_cast<const PrefillPlan*>(ws),
+                     reinterpret_cast<const PrefillSplit*>(ws + w.splits), ws + w.slots,
+                     static_cast<uint16_t*>(a.out), a.num_q_heads, a.num_kv_heads);
   trace_after(a.stream);
   return hipGetLastError();
 }

@@ -1,0 +1,66 @@
+"""Planned prefill steps: tiles whose keys are shared by several workgroups and
+merged, and items ordered over sequences. Against the oracle on every row, and
+against the same call with a workspace that only holds the list of whole tiles."""
+import pytest
+import torch
+
+import paper_2608_23658_amd.kvattn as K
+from workloads import make_batch_from_lens
+from tests.gpu_helpers import (seq_bounds, Dev, assert_parity, oracle_prefill, require_gpu, say)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def _list_bytes(b):
+    """The least workspace a call takes: 8 bytes per tile of 32 rows."""
+    return ((b.total_q_tokens // 32 + b.num_seqs + 1) * 8 + 16 + 255) // 256 * 256
+
+
+def _check(L, N, hq, hkv, seed):
+    b = make_batch_from_lens(L, N, dtype="bf16", num_q_heads=hq, num_kv_heads=hkv,
+                             head_dim=128, block_size=16, seed=seed)
+    d = Dev(b)
+    ws = K.workspace(K.prefill_workspace_bytes(b.num_seqs, b.total_q_tokens, hq, 128))
+    ws.fill_(0xff)                     # no initial contents are needed
+    say("prefill planned", L[:4], N[:4], hq, hkv)
+    ref = oracle_prefill(b)
+    for what, w in (("planned", ws), ("planned again", ws),
+                    ("whole tiles", K.workspace(_list_bytes(b)))):
+        assert w is ws or w.numel() < ws.numel()
+        out = d.prefill(ws=w, out=torch.full_like(d.q, float("nan")))
+        torch.cuda.synchronize()
+        assert_parity(out, ref, "bf16", f"{what} {hq}/{hkv}", seq_bounds(b))
+
+
+# 16 pieces of one tile; pieces that do not divide the steps; the last tile of
+# one row; a length that ends inside a block; a sequence too short to share
+@pytest.mark.parametrize("hq,hkv", [(8, 1), (4, 1), (2, 1), (1, 1), (12, 3), (32, 8), (64, 8)])
+def test_shared_tiles(hq, hkv):
+    _check([4096, 2111, 640, 70], [33, 65, 200, 9], hq, hkv, seed=301)
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (8, 8)])
+def test_one_short_chunk_over_a_long_context(hq, hkv):
+    _check([6351], [201], hq, hkv, seed=302)
+
+
+def test_more_sequences_than_one_planning_pass_holds():
+    n = [1 + s % 3 for s in range(1100)]
+    _check([x + s % 130 for s, x in enumerate(n)], n, 4, 1, seed=303)
+
+
+def test_more_tiles_than_threads_plan_at_once():
+    _check([17600, 900], [17600, 700], 8, 1, seed=304)
+
+
+def test_a_workspace_below_the_tile_list_is_refused():
+    b = make_batch_from_lens([900], [300], dtype="bf16", num_q_heads=8, num_kv_heads=2,
+                             head_dim=128, block_size=16, seed=305)
+    with pytest.raises(K.KvAttnError) as e:
+        Dev(b).prefill(ws=torch.empty(_list_bytes(b) - 1, dtype=torch.uint8, device="cuda"))
+    assert e.value.code == K.KV_ERR_INVALID
