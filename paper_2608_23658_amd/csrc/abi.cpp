@@ -300,7 +300,7 @@ size_t prefill_min_bytes(int num_seqs, int total_q_tokens) {
 extern "C" size_t kvattn_prefill_workspace_bytes(int num_seqs, int total_q_tokens,
                                                  int num_q_heads, int head_dim) {
   if (num_seqs < 0 || total_q_tokens < 0 || num_q_heads <= 0 || head_dim <= 0) return 0;
-  return align256(kvattn::prefill_planned_bytes(num_seqs, total_q_tokens));
+  return align256(kvattn::prefill_planned_bytes(num_seqs, total_q_tokens, num_q_heads));
 }
 
 extern "C" int kvattn_prefill_chunk(const void* q, const void* kv_layer, int num_blocks,

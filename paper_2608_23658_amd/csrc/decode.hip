@@ -278,28 +278,22 @@ void decode_split_kernel(
   // ---- merge the wavefronts' states (log-sum-exp, in context order) ----
   for (int e = threadIdx.x; e < G * D; e += W * kWave) {
     const int h = e / D, d = e % D;
-    float m = -INFINITY;
-    for (int j = 0; j < parts; ++j) m = fmaxf(m, ml_lds[j][h].x);
-    const float ref = (m == -INFINITY) ? 0.f : m;
-    float l = 0.f, o = 0.f;
-    for (int j = 0; j < parts; ++j) {
-      const float2 ml = ml_lds[j][h];
-      const float w = fast_exp2(ml.x - ref);
-      l = fmaf(w, ml.y, l);
-      o = fmaf(w, o_lds[j][e], o);
-    }
-    if (nsplit == 1) {
-      const float inv = l > 0.f ? 1.f / l : 0.f;
-      uint8_t* orow = out + ((size_t)s * num_q_heads + h0 + h) * row_bytes;
-      if constexpr (BF16)
-        reinterpret_cast<uint16_t*>(orow)[d] = to_bf16(o * inv);
-      else
-        reinterpret_cast<float*>(orow)[d] = o * inv;
-    } else {
-      const size_t idx = ((size_t)s * num_q_heads + h0 + h) * max_splits + split;
-      ws_o[idx * D + d] = o;
-      if (d == 0) ws_ml[idx] = make_float2(m, l);
-    }
+    merge_states(
+        parts, [&](int j) { return o_lds[j][e]; }, [&](int j) { return ml_lds[j][h]; },
+        [&](float m, float l, float o) {
+          if (nsplit == 1) {
+            const float inv = l > 0.f ? 1.f / l : 0.f;
+            uint8_t* orow = out + ((size_t)s * num_q_heads + h0 + h) * row_bytes;
+            if constexpr (BF16)
+              reinterpret_cast<uint16_t*>(orow)[d] = to_bf16(o * inv);
+            else
+              reinterpret_cast<float*>(orow)[d] = o * inv;
+          } else {
+            const size_t idx = ((size_t)s * num_q_heads + h0 + h) * max_splits + split;
+            ws_o[idx * D + d] = o;
+            if (d == 0) ws_ml[idx] = make_float2(m, l);
+          }
+        });
   }
 }
 

@@ -79,7 +79,7 @@ hipError_t launch_copy_blocks(const CopyArgs& a);
 // size 8; the workspace's tile list is sized for it.
 constexpr int kPrefillRows = 32;
 
-// Workspace of a planned prefill step, whatever its head counts.
-size_t prefill_planned_bytes(int num_seqs, int total_q_tokens);
+// Workspace of a planned prefill step, whatever its kv head count.
+size_t prefill_planned_bytes(int num_seqs, int total_q_tokens, int num_q_heads);
 
 }  // namespace kvattn

@@ -43,6 +43,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "decode_walk.hpp"
 #include "launch.hpp"
 
 namespace kvattn {
@@ -205,10 +206,22 @@ __global__ __launch_bounds__(256) void prefill_tile_map_kernel(const int* __rest
 //   9 chunks of 100 to 900 rows over 1000 to 8000 tokens           443 -> 367 us
 //   8192 rows over 24576 (four even rounds, not shared)           3274, 3278 us
 
+//
+// A sequence that adds one row (a decode sequence in a unified step) is no tile:
+// its tile would put one row of each head through 32-row products and stage its
+// whole context through LDS for them. It takes decode's walk instead, a
+// workgroup's eight wavefronts sharing an item's tokens. Such items are bound by
+// HBM and tiles by the matrix units, so the plan lets them run side by side. A
+// call at 32 query heads over 8, one-row sequences as tiles against this:
+//   2048 rows over 6144 cached tokens, 128 one-row of 1024 to 8192   645 -> 435 us
+//   8192 rows over 24576, the same 128                             3667 -> 3477 us
+//   two chunks of 5 and 9 rows, 100 one-row of 1024 to 8192          371 -> 306 us
+//   64 query heads: 512 rows over 1000, 40 one-row of 1024 to 8192   268 -> 142 us
+
 struct PrefillItem {
-  int s, q0;        // sequence, first row of the tile in the chunk
-  int i0, i1;       // key steps, i0 even
-  int slot;         // partial slot, -1: the whole tile, written to out
+  int s, q0;        // sequence, first row of the tile in the chunk (-1: one-row item)
+  int i0, i1;       // key steps, i0 even (one-row item: tokens, i0 a multiple of 64)
+  int slot;         // partial slot, -1: written to out
   int cu0, n, L;    // the sequence's chunk and clamped length
 };
 
@@ -217,9 +230,12 @@ struct PrefillSplit {   // a tile shared by several items
   int slot0, pieces;
 };
 
+struct RowSplit {       // a one-row sequence shared by several items
+  int row, slot0, pieces, pad;
+};
+
 struct PrefillPlan {
-  int items, splits;
-  int pad[2];
+  int items, splits, row_splits, pad;
 };
 
 // A slot holds, for each of the 8 wavefronts of a tile and its 32 rows, O
@@ -227,11 +243,25 @@ struct PrefillPlan {
 constexpr int kSlotFloats = kWaves * 32 * kD;
 constexpr size_t kSlotBytes = kSlotFloats * sizeof(float) + kWaves * 32 * sizeof(float2);
 
+// A one-row slot: O [G][kD] and (max, row sum) [G], whole 16 bytes.
+constexpr size_t row_slot_bytes(int group) {
+  return ((size_t)group * (kD * sizeof(float) + sizeof(float2)) + 15) & ~size_t(15);
+}
+
 constexpr int kPlanThreads = 512;
 constexpr int kPlanCandidates = 16;
 // Estimated cost, in key steps, of an item's prologue and epilogue, and of
 // writing and merging a partial.
 constexpr int kItemSteps = 3, kPartialSteps = 6;
+// A one-row item's time per 64 tokens and kv head, in key steps: on its CU
+// (eight wavefronts, a step of about 2 us each), and of the whole chip's HBM
+// time (32 KiB at 4.6 TB/s: the tiles beside it read too). 2048 rows over 6144
+// cached tokens with 128 one-row sequences of 1024 to 8192: 502 / 443 / 435 /
+// 502 us at 0.15 / 0.3 / 0.5 / 0.8 with the HBM term at 0.0031, and 441 / 439 /
+// 430 / 438 us at 0.0015 / 0.0031 / 0.0045 / 0.006; 512 rows over 1000 with 40
+// of them 141 / 141 / 149 / 150 us and 141 / 141 / 143 / 143.
+constexpr float kRowStep = 0.3f, kRowHbmStep = 0.0042f;
+constexpr int kRowTokens = 1024;   // fewest tokens of a shared sequence's item
 constexpr int kCombineParts = 4;   // workgroups over the dims of a merge
 constexpr int kCombineGrid = 1024;
 
@@ -240,21 +270,33 @@ struct PlanArgs {
   const int* seq_lens;
   int num_seqs, total_q, rows_per_tile, num_kv_heads, max_seq_tokens;
   int max_items, max_slots;   // max_slots 0: no tile is shared
+  int rows, max_row_slots;    // rows 0: one-row sequences are tiles
   PrefillItem* items;
   PrefillSplit* splits;
+  RowSplit* row_splits;
   PrefillPlan* head;
 };
 
 // Steps per item and items of a tile of N steps, at most C steps per item.
 __device__ __forceinline__ int2 tile_pieces(int N, int C) {
-  const int p = (N + C - 1) / C;
-  if (p <= 1) return make_int2(N, 1);
+  const int p = (N - 1) / C + 1;
+  if (N <= 0 || p <= 1) return make_int2(max(N, 0), 1);
   const int per = (((N + p - 1) / p) + 1) & ~1;   // whole pairs of steps
   return make_int2(per, (N + per - 1) / per);
 }
 
-// Exclusive prefix sum over the workgroup; *total gets the sum.
-__device__ __forceinline__ int plan_scan(int v, int* lds, int* total) {
+// Tokens per item and items of a one-row sequence of L tokens, at most C
+// tokens (a multiple of 64) per item.
+__device__ __forceinline__ int2 row_pieces(int L, int C) {
+  const int p = (L - 1) / C + 1;
+  if (L <= 0 || p <= 1) return make_int2(max(L, 0), 1);
+  const int per = ((L - 1) / p / kKeys + 1) * kKeys;
+  return make_int2(per, (L - 1) / per + 1);
+}
+
+// Exclusive prefix sum of v over the workgroup; *total gets the sum and *flags
+// the number of threads with flag set.
+__device__ __forceinline__ int plan_scan(int v, bool flag, int2* lds, int* total, int* flags) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   int x = v;
 #pragma unroll
@@ -262,16 +304,20 @@ __device__ __forceinline__ int plan_scan(int v, int* lds, int* total) {
     const int y = __shfl_up(x, o, kWave);
     x += lane >= o ? y : 0;
   }
-  if (lane == kWave - 1) lds[wave] = x;
+  const int set = __popcll(__ballot(flag));
+  if (lane == kWave - 1) lds[wave] = make_int2(x, set);
   __syncthreads();
-  int before = 0, all = 0;
+  int before = 0, all = 0, count = 0;
 #pragma unroll
   for (int w = 0; w < kPlanThreads / kWave; ++w) {
-    before += w < wave ? lds[w] : 0;
-    all += lds[w];
+    const int2 e = lds[w];
+    before += w < wave ? e.x : 0;
+    all += e.x;
+    count += e.y;
   }
   __syncthreads();
-  *total = all;
+  *total = __builtin_amdgcn_readfirstlane(all);
+  *flags = __builtin_amdgcn_readfirstlane(count);
   return before + x - v;
 }
 
@@ -281,20 +327,38 @@ struct PlanTile {
   int idx, q0, N;
 };
 
-// Latency-bound, one workgroup ahead of the attention kernel. While the
+struct PlanChoice {
+  int limit, x, y;              // steps per item; CUs / kv heads for tiles, for one-row items
+  float tile_time, row_time;    // a tile item's time; a one-row item's on its CU
+};
+
+// Latency-bound, one workgroup ahead of the attention kernel. kResident: the
 // sequences fit one chunk (512) and their tiles one per thread, the usual case,
-// each thread keeps its tile in registers over all passes: 5.0 us (6.6 with
-// candidates to weigh) where finding the tiles again in each pass and one
-// thread weighing the candidates took 10.3 and 15.1; the tile map takes 4.7.
-__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) {
+// and each thread keeps its tile in registers over all passes: 5.5 us, 7.2 with
+// candidates to weigh and 12 with one-row sequences to mix in, where finding the
+// tiles again in each pass and one thread weighing the candidates took 10.3 and
+// 15.1 for the first two; the tile map takes 4.7.
+template <bool kResident>
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs args) {
   __shared__ int seq_cu[kPlanThreads], seq_n[kPlanThreads], seq_L[kPlanThreads];
   __shared__ int first[kPlanThreads + 1];     // first tile of each sequence of the chunk
-  __shared__ int scan_lds[kPlanThreads / kWave];
-  __shared__ int hist[256], steps[kPlanThreads];
-  __shared__ unsigned long long sum_steps;
-  __shared__ int max_steps, best_c, next_slot, next_split;
+  __shared__ int2 scan_lds[kPlanThreads / kWave];
+  __shared__ int hist[256], row_hist[256], steps[kPlanThreads];
+  __shared__ float sum_steps, sum_tokens;
+  __shared__ int max_steps, max_tokens, num_rows, extra_row_items, next_slot, next_split, next_row_slot,
+      next_row_split, row_slots_needed;
   __shared__ int cand_items[kPlanCandidates], cand_slots[kPlanCandidates];
+  __shared__ PlanChoice choice;
   const int tid = threadIdx.x;
+  PlanArgs a = args;
+  if constexpr (!kResident) {
+    // kept in vector registers: the nested loops leave too few scalar ones
+    __shared__ PlanArgs lds_args;
+    if (tid == 0) lds_args = args;
+    __syncthreads();
+    a = lds_args;
+    a.num_seqs = args.num_seqs;   // the bound of the loops with barriers stays uniform
+  }
   const int R = a.rows_per_tile;
   const int seqs = min(a.num_seqs, kPlanThreads);   // sequences of a chunk, at most
 
@@ -302,20 +366,22 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
   auto load_chunk = [&](int base) {
     const int s = base + tid;
     int nt = 0;
+    bool row = false;
     if (s < a.num_seqs) {
       const int len = a.seq_lens[s];
       const int2 r = chunk_rows(a.cu, s, a.total_q);
       seq_cu[tid] = r.x;
       seq_n[tid] = r.y - r.x;
       seq_L[tid] = min(max(len, 0), a.max_seq_tokens);
-      nt = (r.y - r.x + R - 1) / R;
+      row = a.rows && r.y - r.x == 1;
+      nt = row ? 0 : (r.y - r.x + R - 1) / R;
     }
-    int total;
-    const int at = plan_scan(nt, scan_lds, &total);
+    int2 total;
+    const int at = plan_scan(nt, row, scan_lds, &total.x, &total.y);
     first[tid] = at;
-    if (tid == 0) first[kPlanThreads] = total;
+    if (tid == 0) first[kPlanThreads] = total.x;
     __syncthreads();
-    return total;
+    return total;   // tiles and one-row sequences
   };
   // The rows of a sequence are taken in descending order.
   auto tile_of = [&](int t) {
@@ -334,126 +400,256 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
     return r;
   };
 
-  if (tid == 0) { sum_steps = 0; max_steps = 1; next_slot = 0; next_split = 0; }
-  if (tid < 256) hist[tid] = 0;
-  int chunk_tiles = load_chunk(0);   // its barriers also publish the zeros above
-  const bool one_chunk = a.num_seqs <= kPlanThreads;
-  const bool resident = one_chunk && chunk_tiles <= kPlanThreads;   // a tile per thread
+  if (tid == 0) {
+    sum_steps = 0.f;
+    sum_tokens = 0.f;
+    num_rows = 0;
+    max_steps = 1;
+    max_tokens = 1;
+    extra_row_items = 0;
+    next_slot = 0;
+    next_split = 0;
+    next_row_slot = 0;
+    next_row_split = 0;
+    row_slots_needed = 0;
+  }
+  if (tid < 256) {
+    hist[tid] = 0;
+    row_hist[tid] = 0;
+  }
+  const int2 found = load_chunk(0);   // its barriers also publish the zeros above
+  // tiles (of all kv heads) that run at once, one workgroup per CU
+  const int lanes = max(1, kNumCUs / a.num_kv_heads);
+  int chunk_tiles = kResident ? min(found.x, kPlanThreads) : found.x, all_tiles = chunk_tiles;
   PlanTile own = {0, 0, 0};
-  if (resident) {
+  if constexpr (kResident) {
     if (tid < chunk_tiles) own = tile_of(tid);
     steps[tid] = own.N;
-  }
-  // Runs f(base, tile) over every tile, tiles dealt to the threads in turn.
-  auto each_tile = [&](auto f) {
-    if (resident) {
-      if (tid < chunk_tiles) f(0, own);
+    if (a.max_slots == 0 && found.y == 0 && chunk_tiles <= min(lanes, a.max_items)) {
+      // whole tiles that all run at once: any order does
+      if (tid < chunk_tiles)
+        a.items[tid] = {own.idx, own.q0, 0, own.N, -1, seq_cu[own.idx], seq_n[own.idx],
+                        seq_L[own.idx]};
+      if (tid == 0) *a.head = {chunk_tiles, 0, 0, 0};
       return;
     }
-    for (int base = 0; base < a.num_seqs; base += kPlanThreads) {
-      if (!one_chunk) chunk_tiles = load_chunk(base);
-      for (int t = tid; t < chunk_tiles; t += kPlanThreads) f(base, tile_of(t));
-      __syncthreads();
+  }
+  // Runs tile(base, t) over every tile, dealt to the threads in turn, and
+  // row(sequence, cu0, L) over every one-row sequence.
+  auto each = [&](auto tile, auto row) {
+    if constexpr (kResident) {
+      if (tid < chunk_tiles) tile(0, own);
+      if (a.rows && tid < a.num_seqs && seq_n[tid] == 1) row(tid, seq_cu[tid], seq_L[tid]);
+    } else {
+      all_tiles = 0;
+      for (int base = 0; base < a.num_seqs; base += kPlanThreads) {
+        chunk_tiles = load_chunk(base).x;
+        all_tiles += chunk_tiles;
+        for (int t = tid; t < chunk_tiles; t += kPlanThreads) tile(base, tile_of(t));
+        if (a.rows && base + tid < a.num_seqs && seq_n[tid] == 1)
+          row(base + tid, seq_cu[tid], seq_L[tid]);
+        __syncthreads();
+      }
     }
   };
 
-  // ---- totals ----
+  // ---- totals (in fp32: they only feed estimates) ----
   {
-    int tiles_seen = 0, mx = 0;
-    unsigned long long st = 0;
-    each_tile([&](int, const PlanTile& t) {
-      st += t.N;
-      mx = max(mx, t.N);
-      ++tiles_seen;
-    });
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-      st += __shfl_xor(st, o, kWave);
-      mx = max(mx, __shfl_xor(mx, o, kWave));
-      tiles_seen += __shfl_xor(tiles_seen, o, kWave);
-    }
+    float st = 0.f, mx = 0.f, tok = 0.f, tok_mx = 0.f, nr = 0.f;
+    each(
+        [&](int, const PlanTile& t) {
+          st += t.N;
+          mx = fmaxf(mx, t.N);
+        },
+        [&](int, int, int L) {
+          nr += 1.f;
+          tok += L;
+          tok_mx = fmaxf(tok_mx, L);
+        });
+    st = wave_sum(st);
+    mx = wave_max(mx);
+    nr = wave_sum(nr);
     if (tid % kWave == 0) {
-      atomicAdd(&sum_steps, st + ((unsigned long long)tiles_seen << 40));
-      atomicMax(&max_steps, mx);
+      atomicAdd(&sum_steps, st);
+      atomicMax(&max_steps, (int)mx);
+    }
+    if (nr > 0.f) {
+      tok = wave_sum(tok);
+      tok_mx = wave_max(tok_mx);
+      if (tid % kWave == 0) {
+        atomicAdd(&sum_tokens, tok);
+        atomicMax(&max_tokens, (int)fminf(tok_mx, 1e9f));
+        atomicAdd(&num_rows, (int)nr);
+      }
     }
   }
   __syncthreads();
-  const int tiles = (int)(sum_steps >> 40), longest = max_steps;
-  const float work_steps = (float)(sum_steps & ((1ull << 40) - 1));
-  // tiles (of all kv heads) that run at once, one workgroup per CU
-  const int lanes = max(1, kNumCUs / a.num_kv_heads);
-  constexpr int kWhole = 1 << 30;
+  const int tiles = all_tiles, longest = max_steps, rows = num_rows;
+  const float steps_sum = sum_steps, tokens_sum = sum_tokens;
+  constexpr int kWhole = 0x7fffffff;
 
-  // ---- how many steps an item gets ----
-  // Candidate k limits an item to 1 / (k + 1) of the longest tile. The time of
-  // each is estimated as the larger of the whole work over the chip and the
-  // rounds its items take; the fewest items within 3% of the best win. A step
-  // with four or more rounds of tiles gains nothing and is not tried.
-  int C = kWhole;
-  if (a.max_slots > 0 && resident && tiles < 4 * lanes) {
+  // ---- one-row sequences: at least two items per CU, whole above that ----
+  int row_c = kWhole, row_items = rows;
+  if (rows > 0 && a.max_row_slots > 0) {
+    row_c = max(kRowTokens, ((int)fminf(tokens_sum / (2 * lanes), 1e9f) / 512 + 1) * 512);
+    if (max_tokens > row_c) {
+      each([](int, const PlanTile&) {},
+           [&](int, int, int L) {
+             const int p = row_pieces(L, row_c).y;
+             if (p > 1) {
+               atomicAdd(&row_slots_needed, p);
+               atomicAdd(&extra_row_items, p - 1);
+             }
+           });
+      __syncthreads();
+      if (row_slots_needed > a.max_row_slots) row_c = kWhole;
+      else row_items += extra_row_items;
+    }
+  }
+  const float row_steps = tokens_sum / 64.f;
+  const float row_work = kRowStep * row_steps + (float)kItemSteps * row_items;
+  const float row_hbm = kRowHbmStep * a.num_kv_heads * row_steps;
+
+  // ---- how many steps an item gets, and how tiles and one-row items mix ----
+  // Candidate k limits an item to 1 / (k + 1) of the longest tile. Its time is
+  // estimated as r rounds of its items on the fewest CUs that do them in r
+  // rounds, while the one-row items run on the others as far as those and HBM
+  // allow, and the rest of them after; without one-row items r is as few as
+  // fit. The fewest items within 3% of the best win. A step with four or more
+  // rounds of tiles gains nothing and is not shared.
+  const bool share = kResident && a.max_slots > 0 && tiles < 4 * lanes;
+  PlanChoice pick = {kWhole, 1, 0, 1.f, 1.f};   // whole tiles, nothing to mix
+  if (share || rows) {
     constexpr int kPer = kPlanThreads / kPlanCandidates;   // 32 lanes per candidate
     auto limit = [&](int k) { return k ? max(4, ((longest + k) / (k + 1) + 1) & ~1) : kWhole; };
-    const int cand = tid / kPer, mine = limit(cand);
-    int items = 0, slots = 0;
-    for (int t = tid % kPer; t < tiles; t += kPer) {
-      const int p = tile_pieces(steps[t], mine).y;
-      items += p;
-      slots += p > 1 ? p : 0;
-    }
+    if (share) {
+      const int cand = tid / kPer, mine = limit(cand);
+      int items = 0, slots = 0;
+      for (int t = tid % kPer; t < tiles; t += kPer) {
+        const int p = tile_pieces(steps[t], mine).y;
+        items += p;
+        slots += p > 1 ? p : 0;
+      }
 #pragma unroll
-    for (int o = kPer / 2; o > 0; o >>= 1) {
-      items += __shfl_xor(items, o, kPer);
-      slots += __shfl_xor(slots, o, kPer);
+      for (int o = kPer / 2; o > 0; o >>= 1) {
+        items += __shfl_xor(items, o, kPer);
+        slots += __shfl_xor(slots, o, kPer);
+      }
+      if (tid % kPer == 0) { cand_items[cand] = items; cand_slots[cand] = slots; }
+    } else if (tid < kPlanCandidates) {
+      cand_items[tid] = tid ? 0 : tiles;
+      cand_slots[tid] = 0;
     }
-    if (tid % kPer == 0) { cand_items[cand] = items; cand_slots[cand] = slots; }
     __syncthreads();
     if (tid < kPlanCandidates) {
       const int n = cand_items[tid], k = cand_slots[tid];
-      const float work = work_steps + (float)kItemSteps * n + (float)kPartialSteps * k;
-      const float est = k > a.max_slots || n == 0
-                            ? INFINITY
-                            : fmaxf(work / lanes, ((n + lanes - 1) / lanes) * (work / n));
+      PlanChoice mine = {kWhole, 1, 0, 1.f, 1.f};
+      float est = INFINITY;
+      if (n > 0 && k <= a.max_slots) {
+        const float work = steps_sum + (float)kItemSteps * n + (float)kPartialSteps * k;
+        const float each = work / n;
+        const int r0 = (n + lanes - 1) / lanes;
+        for (int r = r0; r < r0 + (rows ? 4 : 1); ++r) {
+          const int x = (n + r - 1) / r, y = lanes - x;
+          const float span = r * each;
+          const float done = rows ? fminf(fminf(1.f, y * span / row_work), span / row_hbm) : 1.f;
+          const float e = fmaxf(span, (work + row_work) / lanes) +
+                          (1.f - done) * fmaxf(row_hbm, row_work / lanes);
+          if (e < est) {
+            est = e;
+            mine = {limit(tid), x, y, each, rows ? y * span / fmaxf(done * row_items, 1e-3f) : 1.f};
+          }
+        }
+      }
       float best = est;
 #pragma unroll
       for (int o = kPlanCandidates / 2; o > 0; o >>= 1)
         best = fminf(best, __shfl_xor(best, o, kPlanCandidates));
       const unsigned long long good = __ballot(est <= 1.03f * best);
-      if (tid == 0) best_c = limit(__ffsll(good) - 1);
+      if (tid == __ffsll(good) - 1) choice = mine;
     }
     __syncthreads();
-    C = best_c;
+    pick = choice;
   }
+  const int C = pick.limit;
   const float per_bucket = 255.f / max(1, min(longest, C));   // C bounds an item's steps
+  const float row_per_bucket = 255.f / max(1, min(max_tokens, row_c));
 
   // ---- items in descending length, so that the last to start are short ----
   auto bucket = [&](int per) { return 255 - min(255, (int)(per * per_bucket)); };
-  each_tile([&](int, const PlanTile& t) {
-    const int2 p = tile_pieces(t.N, C);
-    atomicAdd(&hist[bucket(p.x)], p.y);
-  });
+  auto row_bucket = [&](int per) { return 255 - min(255, (int)(per * row_per_bucket)); };
+  each(
+      [&](int, const PlanTile& t) {
+        const int2 p = tile_pieces(t.N, C);
+        atomicAdd(&hist[bucket(p.x)], p.y);
+      },
+      [&](int, int, int L) {
+        const int2 p = row_pieces(L, row_c);
+        atomicAdd(&row_hist[row_bucket(p.x)], p.y);
+      });
   __syncthreads();
-  int total;
-  const int mine = tid < 256 ? hist[tid] : 0;
-  const int at = plan_scan(mine, scan_lds, &total);
+  int total, row_total = 0, unused;
+  const int at = plan_scan(tid < 256 ? hist[tid] : 0, false, scan_lds, &total, &unused);
+  if (rows) {
+    const int row_at =
+        plan_scan(tid < 256 ? row_hist[tid] : 0, false, scan_lds, &row_total, &unused);
+    if (tid < 256) row_hist[tid] = row_at;
+  }
   if (tid < 256) hist[tid] = at;
   __syncthreads();
-  each_tile([&](int base, const PlanTile& t) {
-    const int2 p = tile_pieces(t.N, C);
-    const int j0 = atomicAdd(&hist[bucket(p.x)], p.y);
-    const int cu0 = seq_cu[t.idx], n = seq_n[t.idx], L = seq_L[t.idx];
-    int slot = -1;
-    if (p.y > 1) {
-      slot = atomicAdd(&next_slot, p.y);
-      const int k = atomicAdd(&next_split, 1);
-      a.splits[k] = {cu0 + t.q0, min(R, n - t.q0), slot, p.y};
-    }
-    for (int k = 0; k < p.y; ++k)
-      if (j0 + k < a.max_items)
-        a.items[j0 + k] = {base + t.idx, t.q0, k * p.x, min(t.N, (k + 1) * p.x),
-                           slot < 0 ? -1 : slot + k, cu0, n, L};
-  });
+  // ---- one list in the order of planned starts ----
+  // Tile item j starts at (j / x) dt, one-row item k at (k / y) dd (times in
+  // 1/16 steps); on a tie the tile is first. y 0: one-row items after all tiles.
+  const int x = max(1, pick.x), y = pick.y;
+  const long long dt = max(1, (int)(pick.tile_time * 16.f));
+  const long long dd = max(1, (int)fminf(pick.row_time * 16.f, 1e9f));
+  auto tile_pos = [&](int j) {
+    if (row_total == 0 || y <= 0) return j;
+    const long long before = ((j / x) * dt + dd - 1) / dd * y;
+    return j + (int)min(before, (long long)row_total);
+  };
+  auto row_pos = [&](int k) {
+    if (y <= 0) return total + k;
+    const long long before = ((k / y) * dd / dt + 1) * x;
+    return k + (int)min(before, (long long)total);
+  };
+  each(
+      [&](int base, const PlanTile& t) {
+        const int2 p = tile_pieces(t.N, C);
+        const int j0 = atomicAdd(&hist[bucket(p.x)], p.y);
+        const int cu0 = seq_cu[t.idx], n = seq_n[t.idx], L = seq_L[t.idx];
+        int slot = -1;
+        if (p.y > 1) {
+          slot = atomicAdd(&next_slot, p.y);
+          const int k = atomicAdd(&next_split, 1);
+          a.splits[k] = {cu0 + t.q0, min(R, n - t.q0), slot, p.y};
+        }
+        for (int k = 0; k < p.y; ++k) {
+          const int pos = tile_pos(j0 + k);
+          if (pos < a.max_items)
+            a.items[pos] = {base + t.idx, t.q0, k * p.x, min(t.N, (k + 1) * p.x),
+                            slot < 0 ? -1 : slot + k, cu0, n, L};
+        }
+      },
+      [&](int s, int cu0, int L) {
+        const int2 p = row_pieces(L, row_c);
+        const int k0 = atomicAdd(&row_hist[row_bucket(p.x)], p.y);
+        int slot = -1;
+        if (p.y > 1) {
+          slot = atomicAdd(&next_row_slot, p.y);
+          const int k = atomicAdd(&next_row_split, 1);
+          a.row_splits[k] = {cu0, slot, p.y, 0};
+        }
+        for (int k = 0; k < p.y; ++k) {
+          const int pos = row_pos(k0 + k);
+          if (pos < a.max_items)
+            a.items[pos] = {s, -1, k * p.x, min(L, (k + 1) * p.x), slot < 0 ? -1 : slot + k, cu0,
+                            1, L};
+        }
+      });
   __syncthreads();
-  if (tid == 0) *a.head = {min(total, a.max_items), next_split, {0, 0}};
+  if (tid == 0)
+    *a.head = {min(total + row_total, a.max_items), next_split, next_row_split, 0};
 }
 
 // Merge the partials of the shared tiles: one workgroup per (tile, kv head,
@@ -466,11 +662,31 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
 template <int G>
 __global__ __launch_bounds__(256) void prefill_combine_kernel(
     const PrefillPlan* __restrict__ head, const PrefillSplit* __restrict__ splits,
-    const uint8_t* __restrict__ slots, uint16_t* __restrict__ out, int num_q_heads,
+    const RowSplit* __restrict__ row_splits, const uint8_t* __restrict__ slots,
+    const uint8_t* __restrict__ row_slots, uint16_t* __restrict__ out, int num_q_heads,
     int num_kv_heads) {
   constexpr int kPart = kCombineParts;
   __shared__ uint32_t tile[32][kD / 2 / kPart + 1];
-  const int tasks = head->splits * num_kv_heads * kWaves * kPart;
+  const int row_tasks = head->row_splits * num_kv_heads;
+  for (int task = gridDim.x - 1 - blockIdx.x; task < row_tasks; task += gridDim.x) {
+    const RowSplit sp = row_splits[task / num_kv_heads];
+    const int g = task % num_kv_heads;
+    const size_t stride = (size_t)num_kv_heads * row_slot_bytes(G);
+    const uint8_t* base = row_slots + ((size_t)sp.slot0 * num_kv_heads + g) * row_slot_bytes(G);
+    for (int e = threadIdx.x; e < G * kD; e += 256) {
+      merge_states(
+          sp.pieces, [&](int j) { return reinterpret_cast<const float*>(base + j * stride)[e]; },
+          [&](int j) {
+            return reinterpret_cast<const float2*>(base + j * stride +
+                                                   G * kD * sizeof(float))[e / kD];
+          },
+          [&](float, float l, float o) {
+            const float inv = l > 0.f ? 1.f / l : 0.f;
+            out[((size_t)sp.row * num_q_heads + g * G) * kD + e] = to_bf16(o * inv);
+          });
+    }
+  }
+  const int tasks = head->splits * num_kv_heads * kWaves * kPart;   // of shared tiles
   for (int task = blockIdx.x; task < tasks; task += gridDim.x) {
     const int part = task % kPart;
     const int w = (task / kPart) % kWaves;
@@ -540,40 +756,17 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(
   }
 }
 
+// One item of a work tile.
 template <int G, bool kPow2Blocks>
-__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
-                          amdgpu_waves_per_eu(2, 2)))
-void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ kv,
-                    int num_blocks, const int* __restrict__ block_table,
-                    const int* __restrict__ seq_lens, const int* __restrict__ cu,
-                    uint16_t* __restrict__ out, const int2* __restrict__ tiles,
-                    const int* __restrict__ tile_count, const PrefillItem* __restrict__ items,
-                    uint8_t* __restrict__ slots, int total_q, int num_q_heads, int num_kv_heads,
-                    int max_blocks, int max_seq_len, float scale_log2) {
-  constexpr int kRows = 32 * kWaves / G;   // rows per work tile
-  const int wid = blockIdx.x;
-  const int g = wid % num_kv_heads;
-  const int ti = wid / num_kv_heads;
-  PrefillItem it;
-  if (items) it = items[ti];   // the list has room for the whole grid: read beside the count
-  if (ti >= *tile_count) return;
+__device__ __forceinline__ void prefill_tile(
+    const PrefillItem& it, int g, const uint16_t* __restrict__ q, const uint8_t* __restrict__ kv,
+    int num_blocks, const int* __restrict__ block_table, uint16_t* __restrict__ out,
+    uint8_t* __restrict__ slots, int num_q_heads, int num_kv_heads, int max_blocks,
+    float scale_log2) {
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // uniform per wavefront
   const int lane = tid % kWave;
   const int h = g * G + wave % G;
-  if (!items) {   // no plan: the tile map's whole tiles
-    const int2 tl = tiles[ti];
-    const int2 rows = chunk_rows(cu, tl.x, total_q);
-    it.s = tl.x;
-    it.q0 = tl.y;
-    it.cu0 = rows.x;
-    it.n = rows.y - rows.x;
-    it.L = min(max(seq_lens[tl.x], 0), min(max_seq_len, max_blocks * kBS));
-    const int last_pos = min(it.L - it.n + it.q0 + min(kRows, it.n - it.q0) - 1, it.L - 1);
-    it.i0 = 0;
-    it.i1 = last_pos >= 0 ? last_pos / kKeys + 1 : 0;
-    it.slot = -1;
-  }
   const int s = it.s, q0 = it.q0, cu0 = it.cu0, n = it.n;
   const int L = __builtin_amdgcn_readfirstlane(it.L);
   const int row0 = q0 + (wave / G) * 32;        // first row of this wave
@@ -1055,11 +1248,109 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ 
   }
 }
 
+// One item of a one-row sequence: the eight wavefronts share its tokens evenly
+// in whole steps of 64 and merge their states through LDS.
+template <int G>
+__device__ __forceinline__ void prefill_row(
+    const PrefillItem& it, int g, const uint16_t* __restrict__ q, const uint8_t* __restrict__ kv,
+    int num_blocks, const int* __restrict__ block_table, uint16_t* __restrict__ out,
+    uint8_t* __restrict__ row_slots, int num_q_heads, int num_kv_heads, int max_blocks,
+    float scale_log2) {
+  __shared__ __attribute__((aligned(16))) float o_lds[kWaves][G * kD];
+  __shared__ float2 ml_lds[kWaves][G];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int i0 = it.i0, i1 = it.i1;
+  const int per = max(1, (i1 - i0 + kWaves * kKeys - 1) / (kWaves * kKeys)) * kKeys;
+  const int parts = (i1 - i0 + per - 1) / per;     // wavefronts with tokens
+  const size_t head_off = (size_t)g * kTileBytes;
+  const DecodeTiles<false> tiles = {kv, nullptr, 0, 2 * (size_t)num_kv_heads * kTileBytes,
+                                    head_off, (size_t)num_kv_heads * kTileBytes + head_off};
+  const size_t row = ((size_t)it.cu0 * num_q_heads + g * G) * kD;
+  if (wave < parts) {
+    const int t0 = i0 + wave * per;
+    walk_bf16<kD, G, false>(tiles, q + row, block_table + (size_t)it.s * max_blocks, num_blocks,
+                            t0, min(i1, t0 + per), scale_log2, o_lds[wave], ml_lds[wave]);
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < G * kD; e += kThreads) {
+    merge_states(
+        parts, [&](int j) { return o_lds[j][e]; }, [&](int j) { return ml_lds[j][e / kD]; },
+        [&](float m, float l, float o) {
+          if (it.slot < 0) {
+            const float inv = l > 0.f ? 1.f / l : 0.f;
+            out[row + e] = to_bf16(o * inv);
+          } else {
+            uint8_t* slot = row_slots + ((size_t)it.slot * num_kv_heads + g) * row_slot_bytes(G);
+            reinterpret_cast<float*>(slot)[e] = o;
+            if (e % kD == 0)
+              reinterpret_cast<float2*>(slot + G * kD * sizeof(float))[e / kD] =
+                  make_float2(m, l);
+          }
+        });
+  }
+}
+
+// Work tiles only: one workgroup per (item or tile, kv head).
+template <int G, bool kPow2Blocks>
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
+                          amdgpu_waves_per_eu(2, 2)))
+void prefill_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ kv,
+                    int num_blocks, const int* __restrict__ block_table,
+                    const int* __restrict__ seq_lens, const int* __restrict__ cu,
+                    uint16_t* __restrict__ out, const int2* __restrict__ tiles,
+                    const int* __restrict__ tile_count, const PrefillItem* __restrict__ items,
+                    uint8_t* __restrict__ slots, int total_q, int num_q_heads, int num_kv_heads,
+                    int max_blocks, int max_seq_len, float scale_log2) {
+  constexpr int kRows = 32 * kWaves / G;   // rows per work tile
+  const int g = blockIdx.x % num_kv_heads;
+  const int ti = blockIdx.x / num_kv_heads;
+  PrefillItem it;
+  if (items) it = items[ti];   // the list has room for the whole grid: read beside the count
+  if (ti >= *tile_count) return;
+  if (!items) {   // no plan: the tile map's whole tiles
+    const int2 tl = tiles[ti];
+    const int2 rows = chunk_rows(cu, tl.x, total_q);
+    it.s = tl.x;
+    it.q0 = tl.y;
+    it.cu0 = rows.x;
+    it.n = rows.y - rows.x;
+    it.L = min(max(seq_lens[tl.x], 0), min(max_seq_len, max_blocks * kBS));
+    const int last_pos = min(it.L - it.n + it.q0 + min(kRows, it.n - it.q0) - 1, it.L - 1);
+    it.i0 = 0;
+    it.i1 = last_pos >= 0 ? last_pos / kKeys + 1 : 0;
+    it.slot = -1;
+  }
+  prefill_tile<G, kPow2Blocks>(it, g, q, kv, num_blocks, block_table, out, slots, num_q_heads,
+                               num_kv_heads, max_blocks, scale_log2);
+}
+
+// A planned step that may hold one-row sequences.
+template <int G, bool kPow2Blocks>
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
+                          amdgpu_waves_per_eu(2, 2)))
+void prefill_step_kernel(const uint16_t* __restrict__ q, const uint8_t* __restrict__ kv,
+                         int num_blocks, const int* __restrict__ block_table,
+                         uint16_t* __restrict__ out, const PrefillPlan* __restrict__ head,
+                         const PrefillItem* __restrict__ items, uint8_t* __restrict__ slots,
+                         uint8_t* __restrict__ row_slots, int num_q_heads, int num_kv_heads,
+                         int max_blocks, float scale_log2) {
+  const int g = blockIdx.x % num_kv_heads;
+  const int ti = blockIdx.x / num_kv_heads;
+  const PrefillItem it = items[ti];   // the list has room for the whole grid
+  if (ti >= head->items) return;
+  if (it.q0 < 0)
+    prefill_row<G>(it, g, q, kv, num_blocks, block_table, out, row_slots, num_q_heads,
+                   num_kv_heads, max_blocks, scale_log2);
+  else
+    prefill_tile<G, kPow2Blocks>(it, g, q, kv, num_blocks, block_table, out, slots, num_q_heads,
+                                 num_kv_heads, max_blocks, scale_log2);
+}
+
 // Offsets of a planned step's pieces of the workspace.
 namespace {
 struct PrefillWs {
-  int max_items, max_slots;     // items; slots per kv head
-  size_t items, splits, slots;  // byte offsets; the plan's head is at 0
+  int max_items, max_slots, max_row_slots;   // items; slots per kv head
+  size_t items, splits, row_splits, slots, row_slots;   // byte offsets; the head is at 0
   size_t total;
 };
 
@@ -1068,42 +1359,54 @@ size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // Workgroups' worth of partial slots: the plan fills the chip once or twice.
 constexpr int kSlotWorkgroups = 2 * kNumCUs;
 
-PrefillWs prefill_ws(int num_seqs, int total_q, int rows_per_tile, int num_kv_heads) {
+PrefillWs prefill_ws(int num_seqs, int total_q, int group, int num_kv_heads) {
   PrefillWs w;
+  const int lanes = num_kv_heads < kNumCUs ? kNumCUs / num_kv_heads : 1;
   w.max_slots = num_kv_heads <= kNumCUs ? kSlotWorkgroups / num_kv_heads : 0;
-  w.max_items = total_q / rows_per_tile + num_seqs + w.max_slots;
+  // shared one-row sequences of T tokens in all have at most 2 T / (T / (2 lanes)) items
+  w.max_row_slots = 4 * lanes + 8;
+  w.max_items = total_q / (32 * kWaves / group) + num_seqs + w.max_slots + w.max_row_slots;
   w.items = 256;
   w.splits = w.items + up256((size_t)w.max_items * sizeof(PrefillItem));
-  w.slots = w.splits + up256((size_t)(w.max_slots / 2 + 1) * sizeof(PrefillSplit));
-  w.total = w.slots + (size_t)w.max_slots * num_kv_heads * kSlotBytes;
+  w.row_splits = w.splits + up256((size_t)(w.max_slots / 2 + 1) * sizeof(PrefillSplit));
+  w.slots = w.row_splits + up256((size_t)(w.max_row_slots / 2 + 1) * sizeof(RowSplit));
+  w.row_slots = w.slots + (size_t)w.max_slots * num_kv_heads * kSlotBytes;
+  w.total = w.row_slots + (size_t)w.max_row_slots * num_kv_heads * row_slot_bytes(group);
   return w;
 }
 }  // namespace
 
-size_t prefill_planned_bytes(int num_seqs, int total_q) {
-  // the kv heads are not known here: the most items and slots any count needs
-  const size_t items = (size_t)total_q / kPrefillRows + num_seqs + kSlotWorkgroups;
-  return 256 + up256(items * sizeof(PrefillItem)) +
-         up256((kSlotWorkgroups / 2 + 1) * sizeof(PrefillSplit)) + kSlotWorkgroups * kSlotBytes;
+size_t prefill_planned_bytes(int num_seqs, int total_q, int num_q_heads) {
+  // the most of every group size's layout
+  size_t most = 0;
+  for (int group = 1; group <= 8; group *= 2) {
+    if (num_q_heads % group) continue;
+    const size_t t = prefill_ws(num_seqs, total_q, group, num_q_heads / group).total;
+    most = t > most ? t : most;
+  }
+  return most;
 }
 
 template <int G>
 static hipError_t launch_prefill_t(const PrefillArgs& a) {
   constexpr int kRowsPerTile = 32 * kWaves / G;
   uint8_t* ws = static_cast<uint8_t*>(a.workspace);
-  const PrefillWs w = prefill_ws(a.num_seqs, a.total_q_tokens, kRowsPerTile, a.num_kv_heads);
+  const PrefillWs w = prefill_ws(a.num_seqs, a.total_q_tokens, G, a.num_kv_heads);
   // Sharing tiles needs more than 8 key steps somewhere (below that an item's
   // own cost outweighs what it saves) and fewer than four rounds of tiles. One
   // sequence whose tiles are not shared needs no plan either: the tile map, 1 us
   // faster, lists its tiles in the same order.
   const bool share = a.max_seq_len > 8 * kKeys &&
                      (long long)(a.total_q_tokens / kRowsPerTile) * a.num_kv_heads < 4 * kNumCUs;
-  const bool planned = a.workspace_bytes >= w.total && (a.num_seqs > 1 || share);
+  // Several sequences may hold one-row ones (only the device knows), one does if
+  // it is one row; with one longer sequence the kernel without that branch runs.
+  const bool rows = a.num_seqs > 1 || a.total_q_tokens == 1;
+  const bool planned = a.workspace_bytes >= w.total && (rows || share);
   const long long bound = (long long)a.total_q_tokens / kRowsPerTile + a.num_seqs;
   const int2* tiles = nullptr;
   const int* count;
   const PrefillItem* items = nullptr;
-  int grid_items, max_slots = 0;
+  int grid_items, max_slots = 0, max_row_slots = 0;
   hipError_t e;
   if (planned) {
     max_slots = share ? w.max_slots : 0;
@@ -1115,16 +1418,26 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
     p.rows_per_tile = kRowsPerTile;
     p.num_kv_heads = a.num_kv_heads;
     p.max_seq_tokens = a.max_seq_len < a.max_blocks * kBS ? a.max_seq_len : a.max_blocks * kBS;
-    grid_items = (int)(bound + max_slots);
+    // One-row sequences are shared from 1024 tokens on (a CU's walk of 4 us), or
+    // from 8192 beside four or more rounds of tiles, which such a walk can hide
+    // in; without either, no merge is launched (about 4 us).
+    max_row_slots = rows && a.max_seq_len > (share ? kRowTokens : 8 * kRowTokens)
+                        ? w.max_row_slots : 0;
+    grid_items = (int)(bound + max_slots + max_row_slots);
     p.max_items = grid_items;
     p.max_slots = max_slots;
+    p.rows = rows;
+    p.max_row_slots = max_row_slots;
     p.items = reinterpret_cast<PrefillItem*>(ws + w.items);
     p.splits = reinterpret_cast<PrefillSplit*>(ws + w.splits);
+    p.row_splits = reinterpret_cast<RowSplit*>(ws + w.row_splits);
     p.head = reinterpret_cast<PrefillPlan*>(ws);
     items = p.items;
     count = &p.head->items;
     trace_before(a.stream, "prefill_plan");
-    hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, a.stream, p);
+    const bool resident = a.num_seqs <= kPlanThreads && bound <= kPlanThreads;
+    hipLaunchKernelGGL(resident ? prefill_plan_kernel<true> : prefill_plan_kernel<false>, dim3(1),
+                       dim3(kPlanThreads), 0, a.stream, p);
   } else {
     // One sequence of whole tiles, or a workspace of the tile list's size alone.
     int* c = reinterpret_cast<int*>(ws);
@@ -1145,22 +1458,33 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   trace_before(a.stream, "prefill");
   const unsigned kvh = (unsigned)a.num_kv_heads;
-  auto kernel = (kvh & (kvh - 1)) == 0 ? prefill_kernel<G, true> : prefill_kernel<G, false>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, a.stream,
-                     static_cast<const uint16_t*>(a.q), static_cast<const uint8_t*>(a.kv),
-                     a.num_blocks, a.block_table, a.seq_lens, a.cu_seqlens_q,
-                     static_cast<uint16_t*>(a.out), tiles, count, items, ws + w.slots,
-                     a.total_q_tokens, a.num_q_heads, a.num_kv_heads, a.max_blocks,
-                     a.max_seq_len, a.scale * kLog2e);
+  const bool pow2 = (kvh & (kvh - 1)) == 0;
+  const uint16_t* q = static_cast<const uint16_t*>(a.q);
+  const uint8_t* kv = static_cast<const uint8_t*>(a.kv);
+  uint16_t* out = static_cast<uint16_t*>(a.out);
+  const PrefillPlan* head = reinterpret_cast<const PrefillPlan*>(ws);
+  const float scale_log2 = a.scale * kLog2e;
+  if (planned && rows) {
+    auto kernel = pow2 ? prefill_step_kernel<G, true> : prefill_step_kernel<G, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, a.stream, q, kv,
+                       a.num_blocks, a.block_table, out, head, items, ws + w.slots,
+                       ws + w.row_slots, a.num_q_heads, a.num_kv_heads, a.max_blocks,
+                       scale_log2);
+  } else {
+    auto kernel = pow2 ? prefill_kernel<G, true> : prefill_kernel<G, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, a.stream, q, kv,
+                       a.num_blocks, a.block_table, a.seq_lens, a.cu_seqlens_q, out, tiles, count,
+                       items, ws + w.slots, a.total_q_tokens, a.num_q_heads, a.num_kv_heads,
+                       a.max_blocks, a.max_seq_len, scale_log2);
+  }
   trace_after(a.stream);
   e = hipGetLastError();
-  if (e != hipSuccess || max_slots == 0) return e;
+  if (e != hipSuccess || (max_slots == 0 && max_row_slots == 0)) return e;
   trace_before(a.stream, "prefill_combine");
-  hipLaunchKernelGGL((prefill_combine_kernel<G>),
-                     dim3(kCombineGrid), dim3(256), 0,
-                     a.stream, reinterpret_cast<const PrefillPlan*>(ws),
-                     reinterpret_cast<const PrefillSplit*>(ws + w.splits), ws + w.slots,
-                     static_cast<uint16_t*>(a.out), a.num_q_heads, a.num_kv_heads);
+  hipLaunchKernelGGL((prefill_combine_kernel<G>), dim3(kCombineGrid), dim3(256), 0, a.stream, head,
+                     reinterpret_cast<const PrefillSplit*>(ws + w.splits),
+                     reinterpret_cast<const RowSplit*>(ws + w.row_splits), ws + w.slots,
+                     ws + w.row_slots, out, a.num_q_heads, a.num_kv_heads);
   trace_after(a.stream);
   return hipGetLastError();
 }

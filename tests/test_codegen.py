@@ -133,6 +133,22 @@ def test_prefill_m0_is_saved_and_restored(disassembly):
             assert ins[b + 1] == ("s_mov_b32", f"m0,{saved}"), (name, ins[b + 1])
 
 
+def test_prefill_step_m0_is_saved_and_restored(disassembly):
+    """The planned kernel that also holds the one-row walk runs the same tile
+    code: its gathers come in the same M0-preserving pairs."""
+    fns = _functions(disassembly, "prefill_step_kernel", operands=True)
+    assert len(fns) == 8, sorted(fns)
+    for name, ins in fns.items():
+        gathers = [i for i, (mn, _) in enumerate(ins) if mn == "global_load_lds_dwordx4"]
+        assert gathers and len(gathers) % 2 == 0, name
+        for a, b in zip(gathers[0::2], gathers[1::2]):
+            assert b == a + 3, (name, a, b)
+            saved = ins[a - 3][1].split(",")[0]
+            assert ins[a - 3] == ("s_mov_b32", f"{saved},m0"), (name, ins[a - 3])
+            assert ins[b + 1] == ("s_mov_b32", f"m0,{saved}"), (name, ins[b + 1])
+        assert not [i for i, _ in ins if i.startswith("scratch_")], name
+
+
 def test_no_kernel_spills_registers(disassembly):
     """Every kernel in the library fits its registers: a spill would put
     scratch loads and stores (counted by vmcnt) into the pipelines."""

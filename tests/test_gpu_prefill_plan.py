@@ -1,5 +1,5 @@
 """Planned prefill steps: tiles whose keys are shared by several workgroups and
-merged, and items ordered over sequences. Against the oracle on every row, and
+merged, items ordered over sequences, one-row sequences beside tiles. Against the oracle on every row, and
 against the same call with a workspace that only holds the list of whole tiles."""
 import pytest
 import torch
@@ -56,6 +56,31 @@ def test_more_sequences_than_one_planning_pass_holds():
 
 def test_more_tiles_than_threads_plan_at_once():
     _check([17600, 900], [17600, 700], 8, 1, seed=304)
+
+
+# one-row sequences: shared by several items, up to a split's edges, one token;
+# alone (rows only), one single row, and next to tiles
+@pytest.mark.parametrize("hq,hkv", [(8, 1), (4, 4), (16, 8), (12, 3), (32, 8)])
+@pytest.mark.parametrize("tiles", [False, True])
+def test_one_row_sequences(hq, hkv, tiles):
+    L = [9000, 1, 63, 512, 513, 1024, 1025, 4097] + ([2500, 300] if tiles else [])
+    _check(L, [1] * 8 + ([130, 3] if tiles else []), hq, hkv, seed=306)
+
+
+def test_a_single_row():
+    _check([5000], [1], 8, 2, seed=307)
+
+
+def test_a_one_row_sequence_without_context_gives_zeros():
+    b = make_batch_from_lens([40, 600, 17], [1, 1, 17], dtype="bf16", num_q_heads=8,
+                             num_kv_heads=2, head_dim=128, block_size=16, seed=308)
+    d = Dev(b)
+    d.sl[0] = 0
+    say("prefill one row, length 0")
+    out = d.prefill(out=torch.full_like(d.q, float("nan")))
+    assert (out[0] == 0).all()
+    ref = oracle_prefill(b)
+    assert_parity(out[1:], ref[1:], "bf16", "rows after an empty one")
 
 
 def test_a_workspace_below_the_tile_list_is_refused():
