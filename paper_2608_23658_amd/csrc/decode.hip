@@ -209,7 +209,7 @@ __device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const 
 }
 
 template <int D, int G, bool BF16, bool kTwo = false>
-__global__ __attribute__((amdgpu_flat_work_group_size(kDecodeWaves * kWave, kDecodeWaves * kWave),
+__global__ __attribute__((amdgpu_flat_work_group_size(kWave, kDecodeWaves * kWave),
                           amdgpu_waves_per_eu(2)))
 void decode_split_kernel(
     const uint8_t* __restrict__ q, const uint8_t* __restrict__ kv,
@@ -235,7 +235,7 @@ void decode_split_kernel(
   if (L == 0) {
     if (split == 0) {
       uint4* o = reinterpret_cast<uint4*>(out + ((size_t)s * num_q_heads + h0) * row_bytes);
-      for (int c = threadIdx.x; c < G * D * S::kEsz / 16; c += W * kWave)
+      for (int c = threadIdx.x; c < G * D * S::kEsz / 16; c += blockDim.x)
         o[c] = make_uint4(0, 0, 0, 0);
     }
     return;
@@ -266,7 +266,7 @@ void decode_split_kernel(
   } else {
     __shared__ float p_lds[W][S::kTile * G];
     __shared__ uint4 q_lds[G * S::kKCh];
-    for (int i = threadIdx.x; i < G * S::kKCh; i += W * kWave)
+    for (int i = threadIdx.x; i < G * S::kKCh; i += blockDim.x)
       q_lds[i] = reinterpret_cast<const uint4*>(q_row)[i];
     __syncthreads();
     if (wave < parts)
@@ -276,7 +276,7 @@ void decode_split_kernel(
   __syncthreads();
 
   // ---- merge the wavefronts' states (log-sum-exp, in context order) ----
-  for (int e = threadIdx.x; e < G * D; e += W * kWave) {
+  for (int e = threadIdx.x; e < G * D; e += blockDim.x) {
     const int h = e / D, d = e % D;
     merge_states(
         parts, [&](int j) { return o_lds[j][e]; }, [&](int j) { return ml_lds[j][h]; },
@@ -416,9 +416,13 @@ static hipError_t launch_decode_t(const DecodeArgs& a) {
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   float* ws_o = reinterpret_cast<float*>(a.workspace);
   float2* ws_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(a.workspace) + a.ws_ml_offset);
+  // A context of at most 1, 2 or 3 steps has that many shares of one step each,
+  // so further wavefronts would only wait.
+  const int steps = (a.max_seq_len + 63) / 64;
+  const int waves = steps < 1 ? 1 : steps < kDecodeWaves ? steps : kDecodeWaves;
   trace_before(a.stream, kTwo ? "decode_split_two_tensor" : "decode_split");
   hipLaunchKernelGGL((decode_split_kernel<D, G, BF16, kTwo>), dim3((unsigned)blocks),
-                     dim3(kDecodeWaves * kWave), 0, a.stream, static_cast<const uint8_t*>(a.q),
+                     dim3(waves * kWave), 0, a.stream, static_cast<const uint8_t*>(a.q),
                      static_cast<const uint8_t*>(a.kv), static_cast<const uint8_t*>(a.kv2),
                      a.num_base, a.num_blocks, a.block_table, a.seq_lens,
                      static_cast<uint8_t*>(a.out), ws_o, ws_ml, a.num_seqs, a.num_q_heads,
