@@ -41,6 +41,11 @@ __device__ __forceinline__ uint4 load_nt(const uint4* p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+__device__ __forceinline__ void store_nt(uint4* p, uint4 v) {
+  const u32x4_t w = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(w, reinterpret_cast<u32x4_t*>(p));
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // DPP lane moves within rows of 16 lanes.
