@@ -67,7 +67,10 @@ int kvattn_abi_version(void);
  * Workspace: device memory of at least kvattn_decode_workspace_bytes(...)
  * bytes, owned by the caller, 256-byte aligned, no initial contents needed,
  * must not be used by another call in flight. Returns 0 if the sizes are
- * invalid. */
+ * invalid. For a small batch this includes room for a partial per quarter of a
+ * split; a workspace with room for one per split only (num_seqs * num_q_heads *
+ * splits rows of head_dim + 2 floats, each part rounded up to 256 bytes) is
+ * accepted too, and gives the same bits more slowly. */
 size_t kvattn_decode_workspace_bytes(int num_seqs, int num_q_heads, int head_dim,
                                      int max_seq_len);
 

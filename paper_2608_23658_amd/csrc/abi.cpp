@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -72,9 +73,14 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 struct DecodeWs {
-  size_t ml_offset;
-  size_t total;
+  size_t ml_offset, total;
+  // the layout with a partial per wavefront of a split, which small batches take
+  size_t spread_ml_offset, spread_total;
 };
+
+// The most that layout takes: kSpreadBlocks splits of 8 query heads each.
+constexpr size_t kSpreadBytes =
+    (size_t)kvattn::kSpreadBlocks * 8 * kvattn::kDecodeWaves * (128 + 2) * sizeof(float);
 
 bool decode_ws(int num_seqs, int num_q_heads, int head_dim, int max_seq_len, DecodeWs* w) {
   if (num_seqs < 0 || num_q_heads <= 0 || head_dim <= 0 || max_seq_len < 0) return false;
@@ -84,6 +90,8 @@ bool decode_ws(int num_seqs, int num_q_heads, int head_dim, int max_seq_len, Dec
   w->ml_offset = align256(n * head_dim * sizeof(float));
   w->total = w->ml_offset + align256(n * 2 * sizeof(float));
   if (w->total == 0) w->total = 256;
+  w->spread_ml_offset = align256(kvattn::kDecodeWaves * n * head_dim * sizeof(float));
+  w->spread_total = w->spread_ml_offset + align256(kvattn::kDecodeWaves * n * 2 * sizeof(float));
   return true;
 }
 
@@ -136,7 +144,9 @@ extern "C" int kvattn_decode_split_tokens(int max_seq_len) {
 extern "C" size_t kvattn_decode_workspace_bytes(int num_seqs, int num_q_heads, int head_dim,
                                                 int max_seq_len) {
   DecodeWs w;
-  return decode_ws(num_seqs, num_q_heads, head_dim, max_seq_len, &w) ? w.total : 0;
+  if (!decode_ws(num_seqs, num_q_heads, head_dim, max_seq_len, &w)) return 0;
+  // never less for a larger batch
+  return std::max(w.total, std::min(w.spread_total, kSpreadBytes));
 }
 
 namespace {
@@ -274,6 +284,8 @@ int decode_check(const char* fn, const void* q, const void* kv_layer, const void
   a.bf16 = dtype == KV_BF16;
   a.workspace = workspace;
   a.ws_ml_offset = w.ml_offset;
+  const size_t room = check_workspace ? std::min(workspace_bytes, kSpreadBytes) : kSpreadBytes;
+  a.spread_ml_offset = w.spread_total <= room ? w.spread_ml_offset : 0;
   a.stream = static_cast<hipStream_t>(stream);
   a.kv2 = kv2;
   a.num_base = num_base;

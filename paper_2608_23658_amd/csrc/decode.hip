@@ -20,6 +20,26 @@
 // quarter of 1024 tokens instead of an even share took 55 us on the last).
 // Eight gains 2-3 us on the smallest batches and loses 5% on the full ones.
 //
+// Four wavefronts on one CU ask it for 128 KiB a step, about 2 us whatever the
+// latency is, while a small batch leaves other CUs idle. So up to kSpreadBlocks
+// workgroups (half the CUs) each wavefront's share becomes a workgroup on a CU
+// of its own that loads a step ahead (which alone gained 0.5 us), writes its
+// state as a partial, and the merge kernel does the split's merge first, with
+// the same operations: the results are the same bits. The workgroups of a call
+// before, its time before and after (bf16, 32 query heads over 8, head_dim 128,
+// or 64 over 8, head_dim 64, graph replay):
+//   1 sequence of 3971 (32)         16.3 -> 11.2 us      4 of 3000 to 4000 (128)  18.5 -> 17.3 us
+//   1 of 16000 (128)                19.1 -> 19.0 us      1 of 32000 (256)         27.1 -> 30.5 us
+//   8 of 500 to 2000 (128)          17.5 -> 14.1 us      16 of 1000 to 2000 (256) 22.7 -> 24.7 us
+//   d 64: 1 of 4000 (32)            13.8 -> 10.5 us      4 of 2000 to 4000 (128)  14.9 -> 13.4 us
+// A context of one split needs no merge kernel and is not spread. At head_dim
+// 64 a step's loads are half the registers, so the walk that loads ahead still
+// has two workgroups per CU: it is taken up to kAheadBlocks workgroups (256:
+// 15.2 -> 13.2, 512: 25.0 -> 24.0, 1024: 37.5 -> 35.4 and 23.0 -> 22.0 us), above
+// which it gains or loses 1%. One split's calls lose (2048 workgroups of one
+// step per wavefront 23.4 -> 28.3 us), and so does head_dim 128 (8192: 383 ->
+// 390 us, 512: 41.9 -> 43.7 us).
+//
 // The grid is one-dimensional with the kv head varying fastest and the split
 // slowest, so consecutive workgroups, which the dispatcher deals round-robin to
 // the 8 XCDs, carry equal work: putting the split first would send split k of
@@ -54,7 +74,7 @@
 
 namespace kvattn {
 
-constexpr int kDecodeWaves = 4;   // wavefronts that share one split
+constexpr long long kAheadBlocks = 1024;
 
 // Orders a wavefront's LDS writes before its own later reads by other lanes.
 __device__ __forceinline__ void wave_lds_sync() {
@@ -99,7 +119,7 @@ __device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const 
     for (int j = 1; j < S::kTB; ++j) my_b = (kj == j) ? bid[j] : my_b;
     const bool kvalid = (!tail || tb + lane < t1) && (my_b >= 0);
     uint4 kreg[S::kTB][S::kVI], vreg[S::kTB][S::kVI];
-    load_step(tiles, bid, lane, lane, kreg, vreg);
+    load_step<false>(tiles, bid, lane, lane, kreg, vreg);
 
     // ---- scores ----
     float part[S::kTB][G];
@@ -208,9 +228,17 @@ __device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const 
   }
 }
 
-template <int D, int G, bool BF16, bool kTwo = false>
+// Tokens of a wavefront's share of a split of n tokens: whole steps, spread
+// evenly over the wavefronts.
+__device__ __forceinline__ int share_tokens(int n) {
+  return (n + kDecodeWaves * 64 - 1) / (kDecodeWaves * 64) * 64;
+}
+
+// kSpread: one wavefront's share is a workgroup of its own. kAhead: the walk
+// loads a step ahead. Neither changes a result.
+template <int D, int G, bool BF16, bool kTwo, bool kAhead, bool kSpread>
 __global__ __attribute__((amdgpu_flat_work_group_size(kWave, kDecodeWaves * kWave),
-                          amdgpu_waves_per_eu(2)))
+                          amdgpu_waves_per_eu(kAhead && D == 128 ? 1 : 2)))
 void decode_split_kernel(
     const uint8_t* __restrict__ q, const uint8_t* __restrict__ kv,
     const uint8_t* __restrict__ kv2, int num_base, int num_blocks,
@@ -223,8 +251,10 @@ void decode_split_kernel(
   const int wid = blockIdx.x;
   const int g = wid % num_kv_heads;
   const int s = (wid / num_kv_heads) % num_seqs;
-  const int split = wid / (num_kv_heads * num_seqs);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int piece = wid / (num_kv_heads * num_seqs);
+  const int split = kSpread ? piece / W : piece;
+  const int wave =
+      kSpread ? piece % W : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int h0 = g * G;
   const size_t row_bytes = (size_t)D * S::kEsz;
 
@@ -233,7 +263,7 @@ void decode_split_kernel(
   const int nsplit = (L + split_tokens - 1) / split_tokens;
 
   if (L == 0) {
-    if (split == 0) {
+    if (piece == 0) {
       uint4* o = reinterpret_cast<uint4*>(out + ((size_t)s * num_q_heads + h0) * row_bytes);
       for (int c = threadIdx.x; c < G * D * S::kEsz / 16; c += blockDim.x)
         o[c] = make_uint4(0, 0, 0, 0);
@@ -243,8 +273,7 @@ void decode_split_kernel(
   if (split >= nsplit) return;
   const int s0 = split * split_tokens;                       // the workgroup's tokens
   const int s1 = min(L, s0 + split_tokens);
-  // whole steps, spread evenly over the wavefronts
-  const int part_tokens = ((s1 - s0 + W * S::kTile - 1) / (W * S::kTile)) * S::kTile;
+  const int part_tokens = share_tokens(s1 - s0);
   const int parts = (s1 - s0 + part_tokens - 1) / part_tokens;   // wavefronts with tokens
   const int t0 = s0 + wave * part_tokens;                    // this wavefront's tokens
   const int t1 = min(s1, t0 + part_tokens);
@@ -257,11 +286,27 @@ void decode_split_kernel(
                                    head_off, (size_t)num_kv_heads * tile_bytes + head_off};
   const uint8_t* q_row = q + ((size_t)s * num_q_heads + h0) * row_bytes;
 
-  __shared__ __attribute__((aligned(16))) float o_lds[W][G * D];
-  __shared__ float2 ml_lds[W][G];
+  constexpr int kStates = kSpread ? 1 : W;
+  __shared__ __attribute__((aligned(16))) float o_lds[kStates][G * D];
+  __shared__ float2 ml_lds[kStates][G];
+  if constexpr (kSpread) {   // one share: its state goes out as it is
+    if (wave >= parts) return;
+    walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt, num_blocks,
+                                  t0, t1, scale_log2, o_lds[0], ml_lds[0]);
+    wave_lds_sync();
+    const size_t row = ((size_t)s * num_q_heads + h0) * max_splits + split;
+    for (int e = threadIdx.x; e < G * D / 4; e += kWave) {
+      const int h = e / (D / 4), d4 = e % (D / 4);
+      const size_t idx = (row + (size_t)h * max_splits) * W + wave;
+      reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] =
+          reinterpret_cast<const float4*>(o_lds[0])[e];
+      if (d4 == 0) ws_ml[idx] = ml_lds[0][h];
+    }
+    return;
+  }
   if constexpr (BF16) {
     if (wave < parts)
-      walk_bf16<D, G, kTwo>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt, num_blocks, t0,
+      walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt, num_blocks, t0,
                             t1, scale_log2, o_lds[wave], ml_lds[wave]);
   } else {
     __shared__ float p_lds[W][S::kTile * G];
@@ -304,36 +349,59 @@ void decode_split_kernel(
 // kCombineWaveSplits splits one wavefront does the pair; a longer sequence is
 // shared by the four wavefronts of a workgroup (kWide: one pair per workgroup
 // instead of four), a contiguous quarter of its splits each, merged in LDS.
-// Which of the two is taken depends only on the sequence's own length. At
+// Which of the two is taken depends only on the sequence's own length. kSpread:
+// the partials are those of the wavefronts of a split, at most four. At
 // 131071 tokens (128 splits) the serial loop this replaces took 23.7 us.
 constexpr int kCombineWaves = 4;
 constexpr int kCombineWaveSplits = 8;
 
-template <int D, bool BF16, bool kWide>
+template <int D, bool BF16, bool kWide, bool kSpread>
 __global__ __launch_bounds__(kCombineWaves * kWave) void decode_combine_kernel(
     const float* __restrict__ ws_o, const float2* __restrict__ ws_ml,
     const int* __restrict__ seq_lens, uint8_t* __restrict__ out, int num_seqs,
     int num_q_heads, int max_blocks, int max_seq_len, int split_tokens, int max_splits) {
   constexpr int kLPS = D / 4;            // lanes per split row
   constexpr int kSPL = kWave / kLPS;     // splits per load
-  constexpr int kUnroll = 4;
+  constexpr int kUnroll = kSpread ? 2 : 4;
+  constexpr int W = kSpread ? kDecodeWaves : 1;   // states per split
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int w = kWide ? blockIdx.x : blockIdx.x * kCombineWaves + wave;
   if (w >= num_seqs * num_q_heads) return;
   int L = seq_lens[w / num_q_heads];
   L = min(max(L, 0), min(max_seq_len, max_blocks * 16));
   const int ns = (L + split_tokens - 1) / split_tokens;
-  if (ns <= 1) return;
+  if (ns <= (kSpread ? 0 : 1)) return;
   const bool shared = kWide && ns > kCombineWaveSplits;   // uniform over the workgroup
   if (kWide && !shared && wave != 0) return;
   const int per = shared ? (ns + kCombineWaves - 1) / kCombineWaves : ns;
   const int j0 = shared ? min(ns, wave * per) : 0;
   const int j1 = min(ns, j0 + per);
-  const float2* ml = ws_ml + (size_t)w * max_splits;
-  const float4* po = reinterpret_cast<const float4*>(ws_o + (size_t)w * max_splits * D);
+  const float2* ml = ws_ml + (size_t)w * max_splits * W;
+  const float4* po = reinterpret_cast<const float4*>(ws_o + (size_t)w * max_splits * W * D);
+  // Split j's states, in its workgroup's order and with its operations.
+  auto split_parts = [&](int j) {
+    const int n = min(L, (j + 1) * split_tokens) - j * split_tokens;
+    const int per_part = share_tokens(n);
+    return (n + per_part - 1) / per_part;
+  };
+  auto split_ml = [&](int j) {
+    if constexpr (!kSpread) return ml[j];
+    const int n = split_parts(j);
+    float2 x[W];
+#pragma unroll
+    for (int p = 0; p < W; ++p) x[p] = ml[j * W + min(p, n - 1)];
+    float mj = -INFINITY, lj = 0.f;
+#pragma unroll
+    for (int p = 0; p < W; ++p) mj = fmaxf(mj, x[p].x);
+    const float rj = (mj == -INFINITY) ? 0.f : mj;
+#pragma unroll
+    for (int p = 0; p < W; ++p)
+      if (p < n) lj = fmaf(fast_exp2(x[p].x - rj), x[p].y, lj);
+    return make_float2(mj, lj);
+  };
 
   float m = -INFINITY;
-  for (int j = j0 + lane; j < j1; j += kWave) m = fmaxf(m, ml[j].x);
+  for (int j = j0 + lane; j < j1; j += kWave) m = fmaxf(m, split_ml(j).x);
   m = wave_max(m);
   const float ref = (m == -INFINITY) ? 0.f : m;
   float l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
@@ -341,16 +409,49 @@ __global__ __launch_bounds__(kCombineWaves * kWave) void decode_combine_kernel(
   for (int c = j0; c < j1; c += kWave) {
     float wgt = 0.f;                     // of split c + lane
     if (c + lane < j1) {
-      const float2 x = ml[c + lane];
+      const float2 x = split_ml(c + lane);
       wgt = fast_exp2(x.x - ref);
       l = fmaf(wgt, x.y, l);
     }
     const int cnt = min(kWave, j1 - c);
     for (int j = 0; j < cnt; j += kSPL * kUnroll) {
       float4 v[kUnroll];
+      if constexpr (kSpread) {
+        float4 x[kUnroll][W];
+        float2 y[kUnroll][W];
 #pragma unroll
-      for (int k = 0; k < kUnroll; ++k)   // past the end: the last split, at weight 0
-        v[k] = po[(size_t)(c + min(j + k * kSPL + sub, cnt - 1)) * kLPS + col];
+        for (int k = 0; k < kUnroll; ++k) {
+          const int jj = c + min(j + k * kSPL + sub, cnt - 1);
+#pragma unroll
+          for (int p = 0; p < W; ++p) {
+            const int at = jj * W + min(p, split_parts(jj) - 1);
+            x[k][p] = po[(size_t)at * kLPS + col];
+            y[k][p] = ml[at];
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k) {
+          const int n = split_parts(c + min(j + k * kSPL + sub, cnt - 1));
+          float mj = -INFINITY;
+#pragma unroll
+          for (int p = 0; p < W; ++p) mj = fmaxf(mj, y[k][p].x);
+          const float rj = (mj == -INFINITY) ? 0.f : mj;
+          v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int p = 0; p < W; ++p) {
+            if (p >= n) break;
+            const float wp = fast_exp2(y[k][p].x - rj);
+            v[k].x = fmaf(wp, x[k][p].x, v[k].x);
+            v[k].y = fmaf(wp, x[k][p].y, v[k].y);
+            v[k].z = fmaf(wp, x[k][p].z, v[k].z);
+            v[k].w = fmaf(wp, x[k][p].w, v[k].w);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)   // past the end: the last split, at weight 0
+          v[k] = po[(size_t)(c + min(j + k * kSPL + sub, cnt - 1)) * kLPS + col];
+      }
 #pragma unroll
       for (int k = 0; k < kUnroll; ++k) {
         const int i = j + k * kSPL + sub;
@@ -415,13 +516,25 @@ static hipError_t launch_decode_t(const DecodeArgs& a) {
   const long long blocks = (long long)splits * a.num_kv_heads * a.num_seqs;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   float* ws_o = reinterpret_cast<float*>(a.workspace);
-  float2* ws_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(a.workspace) + a.ws_ml_offset);
+  constexpr bool kCanSpread = BF16 && !kTwo;
+  const bool spread =
+      kCanSpread && max_splits > 1 && blocks <= kSpreadBlocks && a.spread_ml_offset != 0;
+  float2* ws_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(a.workspace) +
+                                            (spread ? a.spread_ml_offset : a.ws_ml_offset));
   // A context of at most 1, 2 or 3 steps has that many shares of one step each,
   // so further wavefronts would only wait.
   const int steps = (a.max_seq_len + 63) / 64;
-  const int waves = steps < 1 ? 1 : steps < kDecodeWaves ? steps : kDecodeWaves;
+  const int waves = spread || steps < 1 ? 1 : steps < kDecodeWaves ? steps : kDecodeWaves;
+  auto split = decode_split_kernel<D, G, BF16, kTwo, false, false>;
+  if constexpr (kCanSpread) {
+    if (spread)
+      split = decode_split_kernel<D, G, BF16, kTwo, true, true>;
+    else if constexpr (D == 64)
+      if (max_splits > 1 && blocks <= kAheadBlocks)
+        split = decode_split_kernel<D, G, BF16, kTwo, true, false>;
+  }
   trace_before(a.stream, kTwo ? "decode_split_two_tensor" : "decode_split");
-  hipLaunchKernelGGL((decode_split_kernel<D, G, BF16, kTwo>), dim3((unsigned)blocks),
+  hipLaunchKernelGGL(split, dim3((unsigned)(spread ? blocks * kDecodeWaves : blocks)),
                      dim3(waves * kWave), 0, a.stream, static_cast<const uint8_t*>(a.q),
                      static_cast<const uint8_t*>(a.kv), static_cast<const uint8_t*>(a.kv2),
                      a.num_base, a.num_blocks, a.block_table, a.seq_lens,
@@ -434,7 +547,13 @@ static hipError_t launch_decode_t(const DecodeArgs& a) {
   // A workgroup holds four pairs while a wavefront can do a pair alone, else one.
   const int pairs = a.num_seqs * a.num_q_heads;
   const bool wide = max_splits > kCombineWaveSplits;
-  auto combine = wide ? decode_combine_kernel<D, BF16, true> : decode_combine_kernel<D, BF16, false>;
+  auto combine = wide ? decode_combine_kernel<D, BF16, true, false>
+                      : decode_combine_kernel<D, BF16, false, false>;
+  if constexpr (kCanSpread) {
+    if (spread)
+      combine = wide ? decode_combine_kernel<D, BF16, true, true>
+                     : decode_combine_kernel<D, BF16, false, true>;
+  }
   trace_before(a.stream, "decode_combine");
   hipLaunchKernelGGL(combine, dim3(wide ? pairs : (pairs + kCombineWaves - 1) / kCombineWaves),
                      dim3(kCombineWaves * kWave), 0, a.stream, ws_o, ws_ml, a.seq_lens,

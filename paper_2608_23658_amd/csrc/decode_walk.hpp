@@ -74,15 +74,16 @@ struct DecodeTiles {
 // The four blocks of a step: each block's K tile and V tile as they lie in
 // memory, 1 KiB per load, the two tiles of a block issued together. Within a
 // V load lane l takes 16-byte chunk v_lane of the KiB. A block without a valid
-// id (< 0) gives zeros.
-template <int kTB, int kVI, bool kTwo>
+// id (< 0) gives zeros, or with kAlways whatever block 0 holds: the loads then
+// sit in no branch, so that a later wait can count them.
+template <bool kAlways, int kTB, int kVI, bool kTwo>
 __device__ __forceinline__ void load_step(const DecodeTiles<kTwo>& t, const int (&bid)[kTB],
                                           int lane, int v_lane, uint4 (&kreg)[kTB][kVI],
                                           uint4 (&vreg)[kTB][kVI]) {
 #pragma unroll
   for (int j = 0; j < kTB; ++j) {
-    if (bid[j] >= 0) {
-      const uint8_t* bp = t.block(bid[j]);
+    if (kAlways || bid[j] >= 0) {
+      const uint8_t* bp = t.block(kAlways ? max(bid[j], 0) : bid[j]);
       const uint4* kp = reinterpret_cast<const uint4*>(bp + t.k_off) + lane;
       const uint4* vp = reinterpret_cast<const uint4*>(bp + t.v_off) + v_lane;
 #pragma unroll
@@ -112,8 +113,10 @@ __device__ __forceinline__ void load_step(const DecodeTiles<kTwo>& t, const int 
 //     consecutive tokens per lane, which one swap of the odd lane rows of the
 //     first block's P with the even rows of the second's gives; the same swap
 //     of the two blocks' V loads gives the matching A operands of 16 dims each.
+// kAhead: the next step's loads are issued before a step's products, into a
+// second set of registers; at most 64 blocks, whose ids one load gives.
 // Leaves the wavefront's state in o_out [G][D] and ml_out [G] (LDS).
-template <int D, int G, bool kTwo>
+template <int D, int G, bool kTwo, bool kAhead>
 __device__ __forceinline__ void walk_bf16(const DecodeTiles<kTwo>& tiles,
                                           const uint16_t* __restrict__ q,
                                           const int* __restrict__ bt, int num_blocks, int t0,
@@ -137,16 +140,11 @@ __device__ __forceinline__ void walk_bf16(const DecodeTiles<kTwo>& tiles,
   // lane's 16 bytes of a V KiB (32 dims x 2 halves): dim l % 32, half l / 32
   const int v_lane = 2 * (lane % 32) + lane / 32;
 
-  for (int tb = t0; tb < t1; tb += S::kTile) {
-    const bool tail = tb + S::kTile > t1;   // the step may end inside a block
-    const int at = (tb - t0) / S::kBS % kWave;
-    if (at == 0 && tb != t0) my_id = walk_ids(bt, tb, t1, num_blocks);
-    int bid[S::kTB];
-#pragma unroll
-    for (int j = 0; j < S::kTB; ++j) bid[j] = __builtin_amdgcn_readlane(my_id, at + j);
-    uint4 kreg[S::kTB][S::kVI], vreg[S::kTB][S::kVI];
-    load_step(tiles, bid, lane, v_lane, kreg, vreg);
-
+  // The products and softmax of one loaded step; tail: it may end inside a
+  // block; zero: a block without a valid id still holds what was loaded for it.
+  auto compute = [&](int tb, const int (&bid)[S::kTB], bool tail, bool zero,
+                     const uint4 (&kreg)[S::kTB][S::kVI],
+                     uint4 (&vreg)[S::kTB][S::kVI]) __attribute__((always_inline)) {
     // ---- scores ----
     float x[S::kTB][4];
 #pragma unroll
@@ -189,6 +187,14 @@ __device__ __forceinline__ void walk_bf16(const DecodeTiles<kTwo>& tiles,
     for (int i = 0; i < 2 * S::kVI; ++i) acc[i] *= alpha;
 
     // ---- p . v, two blocks at a time ----
+    if (zero && __builtin_expect((bid[0] | bid[1] | bid[2] | bid[3]) < 0, 0)) {
+#pragma unroll
+      for (int j = 0; j < S::kTB; ++j) {
+        if (bid[j] >= 0) continue;
+#pragma unroll
+        for (int i = 0; i < S::kVI; ++i) vreg[j][i] = make_uint4(0, 0, 0, 0);
+      }
+    }
     if (tail) {
 #pragma unroll
       for (int j = 0; j < S::kTB; ++j) {
@@ -225,6 +231,48 @@ __device__ __forceinline__ void walk_bf16(const DecodeTiles<kTwo>& tiles,
         acc[2 * i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
             __builtin_bit_cast(bf16x8_t, hi), b, acc[2 * i + 1], 0, 0, 0);
       }
+    }
+  };
+  auto step_ids = [&](int tb, int (&bid)[S::kTB]) __attribute__((always_inline)) {
+    const int at = (tb - t0) / S::kBS % kWave;
+    if (!kAhead && at == 0 && tb != t0) my_id = walk_ids(bt, tb, t1, num_blocks);
+#pragma unroll
+    for (int j = 0; j < S::kTB; ++j) bid[j] = __builtin_amdgcn_readlane(my_id, at + j);
+  };
+
+  if constexpr (!kAhead) {
+    for (int tb = t0; tb < t1; tb += S::kTile) {
+      int bid[S::kTB];
+      uint4 kreg[S::kTB][S::kVI], vreg[S::kTB][S::kVI];
+      step_ids(tb, bid);
+      load_step<false>(tiles, bid, lane, v_lane, kreg, vreg);
+      compute(tb, bid, tb + S::kTile > t1, false, kreg, vreg);
+    }
+  } else {
+    int id_a[S::kTB], id_b[S::kTB];
+    uint4 k_a[S::kTB][S::kVI], v_a[S::kTB][S::kVI], k_b[S::kTB][S::kVI], v_b[S::kTB][S::kVI];
+    int tb = t0;
+    step_ids(tb, id_a);
+    load_step<true>(tiles, id_a, lane, v_lane, k_a, v_a);
+    for (;;) {
+      if (tb + S::kTile >= t1) {
+        compute(tb, id_a, tb + S::kTile > t1, true, k_a, v_a);
+        break;
+      }
+      step_ids(tb + S::kTile, id_b);
+      load_step<true>(tiles, id_b, lane, v_lane, k_b, v_b);
+      __builtin_amdgcn_sched_barrier(0);   // all of them before the step's products
+      compute(tb, id_a, false, true, k_a, v_a);
+      tb += S::kTile;
+      if (tb + S::kTile >= t1) {
+        compute(tb, id_b, tb + S::kTile > t1, true, k_b, v_b);
+        break;
+      }
+      step_ids(tb + S::kTile, id_a);
+      load_step<true>(tiles, id_a, lane, v_lane, k_a, v_a);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(tb, id_b, false, true, k_b, v_b);
+      tb += S::kTile;
     }
   }
 

@@ -7,6 +7,9 @@
 
 namespace kvattn {
 
+constexpr int kDecodeWaves = 4;     // wavefronts that share one split of a context
+constexpr int kSpreadBlocks = 128;  // most splits x kv heads given a workgroup per wavefront
+
 struct DecodeArgs {
   const void* q;
   const void* kv;
@@ -22,6 +25,9 @@ struct DecodeArgs {
   bool bf16;
   void* workspace;
   size_t ws_ml_offset;   // byte offset of the (m, l) partials in the workspace
+  // The same with a partial per wavefront of a split; 0: the workspace has no
+  // room for those.
+  size_t spread_ml_offset;
   hipStream_t stream;
 };
 

@@ -1268,7 +1268,7 @@ __device__ __forceinline__ void prefill_row(
   const size_t row = ((size_t)it.cu0 * num_q_heads + g * G) * kD;
   if (wave < parts) {
     const int t0 = i0 + wave * per;
-    walk_bf16<kD, G, false>(tiles, q + row, block_table + (size_t)it.s * max_blocks, num_blocks,
+    walk_bf16<kD, G, false, false>(tiles, q + row, block_table + (size_t)it.s * max_blocks, num_blocks,
                             t0, min(i1, t0 + per), scale_log2, o_lds[wave], ml_lds[wave]);
   }
   __syncthreads();

@@ -87,3 +87,58 @@ def test_combine_split_counts(hq, hkv, d, dtype):
         torch.cuda.synchronize()
         assert_parity(out, oracle_decode(b), dtype, f"combine {hq}/{hkv}/{d}/{dtype}",
                       seq_bounds(b, decode=True))
+
+
+def _least_workspace(rows, d):
+    """A workspace with a partial per split of `rows` (sequence, head, split) rows."""
+    up = lambda x: -(-x // 256) * 256   # noqa: E731
+    return K.workspace(up(rows * d * 4) + up(rows * 8))
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d", [
+    (EDGES, 8, 1, 128),                       # 42 workgroups: edges of the shares
+    ([1025, 2048, 1793, 3971], 64, 8, 128),   # 128: the most that are spread
+    ([1025, 2048, 1793, 3971], 16, 8, 64),
+    ([9300, 5, 8193], 4, 2, 128),             # the merge in four wavefronts
+    ([69 * 1024 + 7], 2, 1, 64),
+    ([65 * 1024], 1, 1, 128),
+])
+def test_spread_shares_give_the_same_bits(lens, hq, hkv, d):
+    """A small batch's shares as workgroups of their own against the least
+    workspace, which keeps them together; then with an empty sequence, and ids
+    outside the layer, which are skipped though block 0, loaded for them, is NaN."""
+    b = _batch(lens, hq, hkv, d, "bf16", seed=215)
+    dev = Dev(b)
+    say("decode spread", lens, hq, hkv, d)
+    rows = len(lens) * hq * -(-max(lens) // 1024)
+    least = _least_workspace(rows, d)
+    full = K.workspace(K.decode_workspace_bytes(len(lens), hq, d, max(lens)))
+    assert full.numel() >= 4 * rows * (d + 2) * 4
+    full.view(torch.float32).fill_(float("nan"))
+    whole = dev.decode(ws=full)
+    assert_parity(whole, oracle_decode(b), "bf16", f"spread {hq}/{hkv}/{d}",
+                  seq_bounds(b, decode=True))
+    assert torch.equal(whole.view(torch.int16), dev.decode(ws=least).view(torch.int16))
+    dev.bt[dev.bt == 0] = -1
+    dev.bt[0, 3:37:11] = b.num_blocks
+    if len(lens) > 1:
+        dev.sl[1] = 0
+    dev.kv.view(b.num_blocks, -1)[0] = float("nan")
+    some = dev.decode(ws=full)
+    assert torch.isfinite(some).all() and (len(lens) == 1 or not some[1].any())
+    assert torch.equal(some.view(torch.int16), dev.decode(ws=least).view(torch.int16))
+
+
+@pytest.mark.parametrize("seqs", [17, 128, 129])   # 136, 1024 and 1032 workgroups
+def test_loading_ahead_gives_the_same_bits(seqs):
+    """head_dim 64 on both sides of the rules on the number of workgroups: each
+    sequence's bits are those of a batch of the same lengths far above them."""
+    lens = [EDGES[s % len(EDGES)] for s in range(seqs)]
+    b = _batch(lens, 8, 4, 64, "bf16", seed=216)
+    dev = Dev(b)
+    say("decode ahead", seqs)
+    got = dev.decode()
+    many = K.decode(dev.q.repeat(10, 1, 1), dev.kv, b.num_blocks, dev.bt.repeat(10, 1),
+                    dev.sl.repeat(10), num_kv_heads=4, max_seq_len=b.max_seq_len, scale=b.scale)
+    assert torch.equal(got.view(torch.int16), many[:seqs].view(torch.int16))
+    assert_parity(got, oracle_decode(b), "bf16", f"ahead {seqs}", seq_bounds(b, decode=True))
