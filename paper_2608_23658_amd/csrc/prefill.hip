@@ -1419,11 +1419,21 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
   uint8_t* ws = static_cast<uint8_t*>(a.workspace);
   const PrefillWs w = prefill_ws(a.num_seqs, a.total_q_tokens, G, a.num_kv_heads);
   // Sharing tiles needs more than 8 key steps somewhere (below that an item's
-  // own cost outweighs what it saves) and fewer than four rounds of tiles. One
-  // sequence whose tiles are not shared needs no plan either: the tile map, 1 us
-  // faster, lists its tiles in the same order.
-  const bool share = a.max_seq_len > 8 * kKeys &&
-                     (long long)(a.total_q_tokens / kRowsPerTile) * a.num_kv_heads < 4 * kNumCUs;
+  // own cost outweighs what it saves) and fewer than four rounds of tiles. Up to
+  // 64 steps the longest walk, over the part of the last round that is idle, has
+  // to outweigh the wider plan and the merge's launch, about 16 steps a round.
+  // 32 query heads over 8, whole tiles, shared, and not shared by this rule:
+  //   2 of 770 rows over 50                         36 / 38 / 33 us
+  //   9 of 176 over 692, with 2 one-row             38 / 46 / 40 us
+  //   440 rows over 227                             29 / 31 / 27 us
+  // and shared by it: 53 -> 41 us (1673 rows with 15 one-row, 8 query heads over 8).
+  // One sequence whose tiles are not shared needs no plan either: the tile map, 1
+  // us faster, lists its tiles in the same order.
+  const long long steps = ((long long)a.max_seq_len + kKeys - 1) / kKeys;
+  const long long tile_wgs = (long long)(a.total_q_tokens / kRowsPerTile) * a.num_kv_heads;
+  const long long chip = tile_wgs > kNumCUs ? (tile_wgs + kNumCUs - 1) / kNumCUs * kNumCUs : kNumCUs;
+  const bool few = a.max_seq_len > 8 * kKeys && tile_wgs < 4 * kNumCUs;
+  const bool share = few && (steps > 64 || steps * (chip - tile_wgs) > 16 * chip);
   // Several sequences may hold one-row ones (only the device knows), one does if
   // it is one row; with one longer sequence the kernel without that branch runs.
   const bool rows = a.num_seqs > 1 || a.total_q_tokens == 1;
@@ -1444,11 +1454,11 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
     p.rows_per_tile = kRowsPerTile;
     p.num_kv_heads = a.num_kv_heads;
     p.max_seq_tokens = a.max_seq_len < a.max_blocks * kBS ? a.max_seq_len : a.max_blocks * kBS;
-    // One-row sequences are shared from 1024 tokens on (a CU's walk of 4 us), or
-    // from 8192 beside four or more rounds of tiles, which such a walk can hide
-    // in; without either, no merge is launched (about 4 us).
-    max_row_slots = rows && a.max_seq_len > (share ? kRowTokens : 8 * kRowTokens)
-                        ? w.max_row_slots : 0;
+    // One-row sequences are shared from 1024 tokens on (a CU's walk of 4 us), from
+    // 2048 where only they would need the merge's launch (about 4 us), or from
+    // 8192 beside four or more rounds of tiles, which such a walk can hide in.
+    const int shared_from = share ? kRowTokens : few ? 2 * kRowTokens : 8 * kRowTokens;
+    max_row_slots = rows && a.max_seq_len > shared_from ? w.max_row_slots : 0;
     grid_items = (int)(bound + max_slots + max_row_slots);
     p.max_items = grid_items;
     p.max_slots = max_slots;

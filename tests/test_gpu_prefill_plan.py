@@ -67,6 +67,15 @@ def test_one_row_sequences(hq, hkv, tiles):
     _check(L, [1] * 8 + ([130, 3] if tiles else []), hq, hkv, seed=306)
 
 
+# both sides of the rules by which a call shares tiles (17 steps with the chip
+# nearly idle) and one-row sequences (2048 tokens)
+@pytest.mark.parametrize("L,N,hq,hkv", [([1024], [300], 8, 1), ([1089], [300], 8, 1),
+                                        ([1100, 2048], [1100, 1], 32, 8),
+                                        ([1100, 2049], [1100, 1], 32, 8)])
+def test_share_rule_edges(L, N, hq, hkv):
+    _check(L, N, hq, hkv, seed=309)
+
+
 def test_a_single_row():
     _check([5000], [1], 8, 2, seed=307)
 
