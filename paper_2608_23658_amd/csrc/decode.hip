@@ -8,17 +8,19 @@
 // merged in context order through LDS, so a split costs a quarter of the
 // serial walk it cost as one wavefront. What bounds a small batch is that
 // walk's latency (one step's loads in flight per wavefront); what bounds a
-// large one is HBM. Four wavefronts are at least as fast as one at every size
-// tried, so there is no rule on the batch, and a sequence's arithmetic depends
-// only on its own length. Per call, at 1 / 2 / 4 / 8 wavefronts a split
-// (32 query heads over 8 kv heads, head_dim 128, bf16):
-//   1 sequence of 3971 tokens          42 / 25 / 17 / 15 us
-//   8 sequences of 1000 to 2000        50 / 30 / 22 / 19 us
-//   256 sequences of 512 to 4096      402 / 395 / 391 / 410 us
-//   256 sequences of 30 to 300         40 / 36 / 40 / 56 us
-// (measured with q.k and p.v on the vector unit; giving every wavefront a fixed
-// quarter of 1024 tokens instead of an even share took 55 us on the last).
-// Eight gains 2-3 us on the smallest batches and loses 5% on the full ones.
+// large one is HBM. A sequence's arithmetic depends only on its own length. Per
+// call, at 2 / 4 / 8 shares a split (32 query heads over 8 kv heads, head_dim
+// 128, bf16, graph replay):
+//   1 sequence of 1000                13.3 / 9.8 / 8.9 us
+//   8 sequences of 200 to 1000        15.0 / 12.0 / 11.4 us
+//   64 sequences of 200 to 1000       27.3 / 27.2 / 28.6 us
+//   64 sequences of 1000 to 4000       107 / 104 / 107 us
+//   256 sequences of 30 to 300        30.8 / 30.7 / 43.1 us
+//   256 sequences of 512 to 4096       362 / 361 / 363 us
+// Eight gains under 1 us on the smallest batches and loses much on the short
+// contexts of a full one. The merge takes four dims per lane, and an fp32 context
+// of one share leaves from the registers instead (256 sequences of 1 to 64: 11.4
+// -> 9.7 us; the same in fp32 12.1 -> 10.9 us).
 //
 // Four wavefronts on one CU ask it for 128 KiB a step, about 2 us whatever the
 // latency is, while a small batch leaves other CUs idle. So up to kSpreadBlocks
@@ -32,13 +34,14 @@
 //   1 of 16000 (128)                19.1 -> 19.0 us      1 of 32000 (256)         27.1 -> 30.5 us
 //   8 of 500 to 2000 (128)          17.5 -> 14.1 us      16 of 1000 to 2000 (256) 22.7 -> 24.7 us
 //   d 64: 1 of 4000 (32)            13.8 -> 10.5 us      4 of 2000 to 4000 (128)  14.9 -> 13.4 us
-// A context of one split needs no merge kernel and is not spread. At head_dim
-// 64 a step's loads are half the registers, so the walk that loads ahead still
-// has two workgroups per CU: it is taken up to kAheadBlocks workgroups (256:
-// 15.2 -> 13.2, 512: 25.0 -> 24.0, 1024: 37.5 -> 35.4 and 23.0 -> 22.0 us), above
-// which it gains or loses 1%. One split's calls lose (2048 workgroups of one
-// step per wavefront 23.4 -> 28.3 us), and so does head_dim 128 (8192: 383 ->
-// 390 us, 512: 41.9 -> 43.7 us).
+// A call of one split needs no merge kernel and is not spread; in a spread call
+// a context of one share is written by its walk (1 sequence of 37 under a bound
+// of 4096: 8.0 -> 6.4 us). At head_dim 64 a step's loads are half the registers,
+// so the walk that loads ahead still has two workgroups per CU: it is taken up to
+// kAheadBlocks workgroups (256: 15.2 -> 13.2, 512: 25.0 -> 24.0, 1024: 37.5 ->
+// 35.4 and 23.0 -> 22.0 us), above which it gains or loses 1%. One split's calls
+// lose (2048 workgroups of one step per wavefront 23.4 -> 28.3 us), and so does
+// head_dim 128 (8192: 383 -> 390 us, 512: 41.9 -> 43.7 us).
 //
 // The grid is one-dimensional with the kv head varying fastest and the split
 // slowest, so consecutive workgroups, which the dispatcher deals round-robin to
@@ -88,11 +91,13 @@ __device__ __forceinline__ void wave_lds_sync() {
 // swaps; lane t then takes the score of token t of the step. In the dim-major V
 // tile lane l owns dim rows l / R (R = 16-byte chunks per row) and a run of
 // consecutive tokens, whose p reach it through LDS. my_id: the ids of the walk's
-// blocks (at most 64), one per lane.
+// blocks (at most 64), one per lane. whole_out, if not null: the walk is the whole
+// context, and its result goes there (G rows of D) instead of its state to LDS.
 template <int D, int G>
 __device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const uint4* q_lds,
                                          float* p_lds, int my_id, int t0, int t1,
-                                         float scale_log2, float* o_out, float2* ml_out) {
+                                         float scale_log2, float* o_out, float2* ml_out,
+                                         float* whole_out) {
   using S = DecodeShape<D, false>;
   const int lane = threadIdx.x % kWave;
   float m_run[G], l_run[G], acc[S::kVI][G];
@@ -216,6 +221,17 @@ __device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const 
     for (int h = 0; h < G; ++h)
 #pragma unroll
       for (int o = 1; o < S::kR; o <<= 1) acc[i][h] += __shfl_xor(acc[i][h], o, kWave);
+  if (whole_out) {
+    if (vrc != 0) return;
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const float inv = l_tot[h] > 0.f ? 1.f / l_tot[h] : 0.f;
+#pragma unroll
+      for (int i = 0; i < S::kVI; ++i)
+        whole_out[h * D + i * S::kDPI + lane / S::kR] = acc[i][h] * inv;
+    }
+    return;
+  }
   if (vrc == 0) {
 #pragma unroll
     for (int h = 0; h < G; ++h)
@@ -228,10 +244,24 @@ __device__ __forceinline__ void walk_f32(const DecodeTiles<false>& tiles, const 
   }
 }
 
+// Four elements of a row of out (the at-th four), from the unnormalised o and
+// the row sum l.
+template <bool BF16>
+__device__ __forceinline__ void write_row4(uint8_t* out, size_t at, float l, float4 o) {
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  if constexpr (BF16)
+    reinterpret_cast<uint2*>(out)[at] =
+        make_uint2(pack_bf16x2(o.x * inv, o.y * inv), pack_bf16x2(o.z * inv, o.w * inv));
+  else
+    reinterpret_cast<float4*>(out)[at] =
+        make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+}
+
 // Tokens of a wavefront's share of a split of n tokens: whole steps, spread
 // evenly over the wavefronts.
+constexpr int kStepTokens = 64;
 __device__ __forceinline__ int share_tokens(int n) {
-  return (n + kDecodeWaves * 64 - 1) / (kDecodeWaves * 64) * 64;
+  return (n + kDecodeWaves * kStepTokens - 1) / (kDecodeWaves * kStepTokens) * kStepTokens;
 }
 
 // kSpread: one wavefront's share is a workgroup of its own. kAhead: the walk
@@ -252,7 +282,6 @@ void decode_split_kernel(
   const int g = wid % num_kv_heads;
   const int s = (wid / num_kv_heads) % num_seqs;
   const int piece = wid / (num_kv_heads * num_seqs);
-  const int split = kSpread ? piece / W : piece;
   const int wave =
       kSpread ? piece % W : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int h0 = g * G;
@@ -270,16 +299,7 @@ void decode_split_kernel(
     }
     return;
   }
-  if (split >= nsplit) return;
-  const int s0 = split * split_tokens;                       // the workgroup's tokens
-  const int s1 = min(L, s0 + split_tokens);
-  const int part_tokens = share_tokens(s1 - s0);
-  const int parts = (s1 - s0 + part_tokens - 1) / part_tokens;   // wavefronts with tokens
-  const int t0 = s0 + wave * part_tokens;                    // this wavefront's tokens
-  const int t1 = min(s1, t0 + part_tokens);
-
   const int* bt = block_table + (size_t)s * max_blocks;
-
   const size_t tile_bytes = (size_t)S::kTileElems * S::kEsz;
   const size_t head_off = (size_t)g * tile_bytes;
   const DecodeTiles<kTwo> tiles = {kv, kv2, num_base, 2 * (size_t)num_kv_heads * tile_bytes,
@@ -289,54 +309,75 @@ void decode_split_kernel(
   constexpr int kStates = kSpread ? 1 : W;
   __shared__ __attribute__((aligned(16))) float o_lds[kStates][G * D];
   __shared__ float2 ml_lds[kStates][G];
+
+  const int split = kSpread ? piece / W : piece;
+  if (split >= nsplit) return;
+  const int s0 = split * split_tokens;                       // the split's tokens
+  const int s1 = min(L, s0 + split_tokens);
+  const int part_tokens = share_tokens(s1 - s0);
+  const int parts = (s1 - s0 + part_tokens - 1) / part_tokens;   // shares with tokens
+  const bool whole = nsplit == 1 && parts == 1;   // a context of one share: nothing to merge
+
   if constexpr (kSpread) {   // one share: its state goes out as it is
     if (wave >= parts) return;
-    walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt, num_blocks,
-                                  t0, t1, scale_log2, o_lds[0], ml_lds[0]);
+    const int t0 = s0 + wave * part_tokens;
+    walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt,
+                                  num_blocks, t0, min(s1, t0 + part_tokens), scale_log2,
+                                  o_lds[0], ml_lds[0]);
     wave_lds_sync();
-    const size_t row = ((size_t)s * num_q_heads + h0) * max_splits + split;
+    const size_t row = (size_t)s * num_q_heads + h0;
     for (int e = threadIdx.x; e < G * D / 4; e += kWave) {
       const int h = e / (D / 4), d4 = e % (D / 4);
-      const size_t idx = (row + (size_t)h * max_splits) * W + wave;
-      reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] =
-          reinterpret_cast<const float4*>(o_lds[0])[e];
-      if (d4 == 0) ws_ml[idx] = ml_lds[0][h];
+      const float4 o = reinterpret_cast<const float4*>(o_lds[0])[e];
+      if (whole) {
+        write_row4<BF16>(out, (row + h) * (D / 4) + d4, ml_lds[0][h].y,
+                         fma_each(1.f, o, float4{}));
+      } else {
+        const size_t idx = ((row + h) * max_splits + split) * W + wave;
+        reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] = o;
+        if (d4 == 0) ws_ml[idx] = ml_lds[0][h];
+      }
     }
     return;
   }
   if constexpr (BF16) {
-    if (wave < parts)
-      walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt, num_blocks, t0,
-                            t1, scale_log2, o_lds[wave], ml_lds[wave]);
+    if (wave < parts) {
+      const int t0 = s0 + wave * part_tokens;
+      walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt,
+                                    num_blocks, t0, min(s1, t0 + part_tokens), scale_log2,
+                                    o_lds[wave], ml_lds[wave]);
+    }
   } else {
     __shared__ float p_lds[W][S::kTile * G];
     __shared__ uint4 q_lds[G * S::kKCh];
     for (int i = threadIdx.x; i < G * S::kKCh; i += blockDim.x)
       q_lds[i] = reinterpret_cast<const uint4*>(q_row)[i];
     __syncthreads();
-    if (wave < parts)
+    float* orow =   // a whole context leaves from the registers
+        whole ? reinterpret_cast<float*>(out) + ((size_t)s * num_q_heads + h0) * D : nullptr;
+    if (wave < parts) {
+      const int t0 = s0 + wave * part_tokens, t1 = min(s1, t0 + part_tokens);
       walk_f32<D, G>(tiles, q_lds, p_lds[wave], walk_ids(bt, t0, t1, num_blocks), t0, t1,
-                     scale_log2, o_lds[wave], ml_lds[wave]);
+                     scale_log2, o_lds[wave], ml_lds[wave], orow);
+    }
+    if (whole) return;
   }
   __syncthreads();
 
-  // ---- merge the wavefronts' states (log-sum-exp, in context order) ----
-  for (int e = threadIdx.x; e < G * D; e += blockDim.x) {
-    const int h = e / D, d = e % D;
-    merge_states(
-        parts, [&](int j) { return o_lds[j][e]; }, [&](int j) { return ml_lds[j][h]; },
-        [&](float m, float l, float o) {
+  // ---- merge the shares' states (log-sum-exp, in context order) ----
+  for (int e = threadIdx.x; e < G * D / 4; e += blockDim.x) {
+    const int h = e / (D / 4), d4 = e % (D / 4);
+    merge_states<float4>(
+        parts, [&](int j) { return reinterpret_cast<const float4*>(o_lds[j])[e]; },
+        [&](int j) { return ml_lds[j][h]; },
+        [&](float m, float l, float4 o) {
+          const size_t row = (size_t)s * num_q_heads + h0 + h;
           if (nsplit == 1) {
-            const float inv = l > 0.f ? 1.f / l : 0.f;
-            uint8_t* orow = out + ((size_t)s * num_q_heads + h0 + h) * row_bytes;
-            if constexpr (BF16)
-              reinterpret_cast<uint16_t*>(orow)[d] = to_bf16(o * inv);
-            else
-              reinterpret_cast<float*>(orow)[d] = o * inv;
+            write_row4<BF16>(out, row * (D / 4) + d4, l, o);
           } else {
-            const size_t idx = ((size_t)s * num_q_heads + h0 + h) * max_splits + split;
-            ws_o[idx * D + d] = o;
-            if (d == 0) ws_ml[idx] = make_float2(m, l);
+            const size_t idx = row * max_splits + split;
+            reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] = o;
+            if (d4 == 0) ws_ml[idx] = make_float2(m, l);
           }
         });
   }
@@ -370,7 +411,7 @@ __global__ __launch_bounds__(kCombineWaves * kWave) void decode_combine_kernel(
   int L = seq_lens[w / num_q_heads];
   L = min(max(L, 0), min(max_seq_len, max_blocks * 16));
   const int ns = (L + split_tokens - 1) / split_tokens;
-  if (ns <= (kSpread ? 0 : 1)) return;
+  if (ns <= 1 && (!kSpread || L <= kStepTokens)) return;   // written by the split kernel
   const bool shared = kWide && ns > kCombineWaveSplits;   // uniform over the workgroup
   if (kWide && !shared && wave != 0) return;
   const int per = shared ? (ns + kCombineWaves - 1) / kCombineWaves : ns;
@@ -499,14 +540,7 @@ __global__ __launch_bounds__(kCombineWaves * kWave) void decode_combine_kernel(
     }
   }
   if (sub != 0) return;
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-  const size_t at = (size_t)w * kLPS + col;
-  if constexpr (BF16)
-    reinterpret_cast<uint2*>(out)[at] =
-        make_uint2(pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv));
-  else
-    reinterpret_cast<float4*>(out)[at] =
-        make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+  write_row4<BF16>(out, (size_t)w * kLPS + col, l, make_float4(o[0], o[1], o[2], o[3]));
 }
 
 template <int D, int G, bool BF16, bool kTwo = false>
@@ -523,7 +557,7 @@ static hipError_t launch_decode_t(const DecodeArgs& a) {
                                             (spread ? a.spread_ml_offset : a.ws_ml_offset));
   // A context of at most 1, 2 or 3 steps has that many shares of one step each,
   // so further wavefronts would only wait.
-  const int steps = (a.max_seq_len + 63) / 64;
+  const int steps = (a.max_seq_len + kStepTokens - 1) / kStepTokens;
   const int waves = spread || steps < 1 ? 1 : steps < kDecodeWaves ? steps : kDecodeWaves;
   auto split = decode_split_kernel<D, G, BF16, kTwo, false, false>;
   if constexpr (kCanSpread) {

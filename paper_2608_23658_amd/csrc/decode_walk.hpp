@@ -34,20 +34,26 @@ __device__ __forceinline__ int walk_ids(const int* __restrict__ bt, int t, int t
   return (unsigned)id < (unsigned)num_blocks ? id : -1;
 }
 
-// Merges n softmax states of one output element in order (log-sum-exp):
-// o_of(j) and ml_of(j) give state j's unnormalised value and (max, row sum);
-// done(m, l, o) gets the merged ones.
-template <typename O, typename Ml, typename Done>
+__device__ __forceinline__ float fma_each(float w, float x, float o) { return fmaf(w, x, o); }
+__device__ __forceinline__ float4 fma_each(float w, float4 x, float4 o) {
+  return make_float4(fmaf(w, x.x, o.x), fmaf(w, x.y, o.y), fmaf(w, x.z, o.z), fmaf(w, x.w, o.w));
+}
+
+// Merges n softmax states of one output element, or of four of one row, in
+// order (log-sum-exp): o_of(j) and ml_of(j) give state j's unnormalised value
+// and (max, row sum); done(m, l, o) gets the merged ones.
+template <typename T, typename O, typename Ml, typename Done>
 __device__ __forceinline__ void merge_states(int n, O o_of, Ml ml_of, Done done) {
   float m = -INFINITY;
   for (int j = 0; j < n; ++j) m = fmaxf(m, ml_of(j).x);
   const float ref = (m == -INFINITY) ? 0.f : m;
-  float l = 0.f, o = 0.f;
+  float l = 0.f;
+  T o = {};
   for (int j = 0; j < n; ++j) {
     const float2 ml = ml_of(j);
     const float w = fast_exp2(ml.x - ref);
     l = fmaf(w, ml.y, l);
-    o = fmaf(w, o_of(j), o);
+    o = fma_each(w, o_of(j), o);
   }
   done(m, l, o);
 }

@@ -674,7 +674,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(
     const size_t stride = (size_t)num_kv_heads * row_slot_bytes(G);
     const uint8_t* base = row_slots + ((size_t)sp.slot0 * num_kv_heads + g) * row_slot_bytes(G);
     for (int e = threadIdx.x; e < G * kD; e += 256) {
-      merge_states(
+      merge_states<float>(
           sp.pieces, [&](int j) { return reinterpret_cast<const float*>(base + j * stride)[e]; },
           [&](int j) {
             return reinterpret_cast<const float2*>(base + j * stride +
@@ -1299,7 +1299,7 @@ __device__ __forceinline__ void prefill_row(
   }
   __syncthreads();
   for (int e = threadIdx.x; e < G * kD; e += kThreads) {
-    merge_states(
+    merge_states<float>(
         parts, [&](int j) { return o_lds[j][e]; }, [&](int j) { return ml_lds[j][e / kD]; },
         [&](float m, float l, float o) {
           if (it.slot < 0) {

@@ -142,3 +142,27 @@ def test_loading_ahead_gives_the_same_bits(seqs):
                     dev.sl.repeat(10), num_kv_heads=4, max_seq_len=b.max_seq_len, scale=b.scale)
     assert torch.equal(got.view(torch.int16), many[:seqs].view(torch.int16))
     assert_parity(got, oracle_decode(b), "bf16", f"ahead {seqs}", seq_bounds(b, decode=True))
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 2, 128, "bf16"), (2, 2, 128, "bf16"),
+                                            (8, 1, 64, "bf16"), (8, 2, 64, "f32")])
+def test_short_contexts_under_any_bound(hq, hkv, d, dtype):
+    """Contexts of one share (written without a merge) and of up to four, under
+    the bounds at which a call's number of wavefronts changes, spread (2048) and
+    not: the same bits as under a bound of two splits that is not spread."""
+    lens = [1, 2, 31, 63, 64, 65, 127, 128, 129, 191, 192, 193, 200, 256, 257, 300, 384, 385]
+    b = _batch(lens, hq, hkv, d, dtype, seed=217)
+    dev = Dev(b)
+    dev.bt = torch.nn.functional.pad(dev.bt, (0, 128 - dev.bt.shape[1]), value=-1).contiguous()
+    kw = dict(num_kv_heads=hkv, scale=b.scale)
+    say("decode short contexts", hq, hkv, d, dtype)
+    least = _least_workspace(len(lens) * hq * 2, d)
+    want = K.decode(dev.q, dev.kv, b.num_blocks, dev.bt, dev.sl, max_seq_len=2048, ws=least, **kw)
+    assert_parity(want, oracle_decode(b), dtype, f"short {hq}/{hkv}/{d}/{dtype}",
+                  seq_bounds(b, decode=True))
+    as_int = torch.int16 if dtype == "bf16" else torch.int32
+    for bound in (64, 65, 128, 129, 192, 193, 300, 385, 1024, 2048):
+        n = sum(L <= bound for L in lens)
+        got = K.decode(dev.q[:n], dev.kv, b.num_blocks, dev.bt[:n], dev.sl[:n],
+                       max_seq_len=bound, **kw)
+        assert torch.equal(got.view(as_int), want[:n].view(as_int)), bound
