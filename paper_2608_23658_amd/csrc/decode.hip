@@ -43,6 +43,29 @@
 // lose (2048 workgroups of one step per wavefront 23.4 -> 28.3 us), and so does
 // head_dim 128 (8192: 383 -> 390 us, 512: 41.9 -> 43.7 us).
 //
+// The grid is sized by max_seq_len, and a caller who captures its calls passes
+// the longest context it will ever meet, so most workgroups can be without
+// tokens. Such a workgroup costs a place on a CU until it has read its length:
+// about 1 ns of the call at four wavefronts, half at two, a third at one. So
+// above kFullBlocks workgroups two wavefronts take turns with a split's shares,
+// above kHalfBlocks one does, and above kMostBlocks a workgroup takes every n-th
+// split of its sequence, n at least kMinPieces so that one long context among
+// many short ones keeps that many workgroups. The shares and merges are the same,
+// and so are the bits. A call at four wavefronts always / by these rules (the
+// workgroups of its bound):
+//   128 sequences of 30 to 500, bound 4096 (4096)      26 us (two: 27.5, one: 29)
+//   256 of 512 to 4096, bound 4096 (8192)              363 / 362 us
+//   256 of 30 to 300, bound 8192 (16384)               43 / 34 us (one: 35.5)
+//   256 of 30 to 300, bound 16384 (32768)              59 / 38 us (two: 43)
+//   64 of 30 to 300, bound 131072 (65536)              67 / 16 us
+//   256 of 200 to 1000, bound 131072 (262144)          318 / 106 us
+//   255 of 30 to 1000 and one of 131071 (262144)       425 / 274 us
+// (kMinPieces 32 / 48 / 64: 315 / 274 / 250 us on the last, but 42 / 50 / 57 us on
+// 256 of 30 to 300, bound 131072).
+// In fp32 four wavefronts lose on short contexts at any bound: up to kShortSteps
+// steps and from kShortBlocks workgroups on two take turns too (32 query heads over 8, head_dim 64: 512 of 30 to
+// 200 54 -> 47 us, 256 of 30 to 300 38 -> 35, 256 of 30 to 400 44 -> 45).
+//
 // The grid is one-dimensional with the kv head varying fastest and the split
 // slowest, so consecutive workgroups, which the dispatcher deals round-robin to
 // the 8 XCDs, carry equal work: putting the split first would send split k of
@@ -71,6 +94,8 @@
 // Partials (m, l, o) of every split go to the workspace; a second kernel merges
 // them (log-sum-exp), in an order that depends only on the sequence's length.
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "decode_walk.hpp"
 #include "launch.hpp"
@@ -78,6 +103,9 @@
 namespace kvattn {
 
 constexpr long long kAheadBlocks = 1024;
+constexpr long long kFullBlocks = 4096, kHalfBlocks = 16384, kMostBlocks = 32768;
+constexpr long long kMinPieces = 48;
+constexpr int kShortSteps = 6, kShortBlocks = 1024;   // fp32
 
 // Orders a wavefront's LDS writes before its own later reads by other lanes.
 __device__ __forceinline__ void wave_lds_sync() {
@@ -265,8 +293,10 @@ __device__ __forceinline__ int share_tokens(int n) {
 }
 
 // kSpread: one wavefront's share is a workgroup of its own. kAhead: the walk
-// loads a step ahead. Neither changes a result.
-template <int D, int G, bool BF16, bool kTwo, bool kAhead, bool kSpread>
+// loads a step ahead. kTurns: a workgroup of fewer wavefronts than shares, which
+// take turns, and with a piece of the context instead of one split. None of
+// them changes a result.
+template <int D, int G, bool BF16, bool kTwo, bool kAhead, bool kSpread, bool kTurns>
 __global__ __attribute__((amdgpu_flat_work_group_size(kWave, kDecodeWaves * kWave),
                           amdgpu_waves_per_eu(kAhead && D == 128 ? 1 : 2)))
 void decode_split_kernel(
@@ -310,76 +340,87 @@ void decode_split_kernel(
   __shared__ __attribute__((aligned(16))) float o_lds[kStates][G * D];
   __shared__ float2 ml_lds[kStates][G];
 
-  const int split = kSpread ? piece / W : piece;
+  int split = kSpread ? piece / W : piece;
   if (split >= nsplit) return;
-  const int s0 = split * split_tokens;                       // the split's tokens
-  const int s1 = min(L, s0 + split_tokens);
-  const int part_tokens = share_tokens(s1 - s0);
-  const int parts = (s1 - s0 + part_tokens - 1) / part_tokens;   // shares with tokens
-  const bool whole = nsplit == 1 && parts == 1;   // a context of one share: nothing to merge
+  for (;;) {
+    const int s0 = split * split_tokens;                       // the split's tokens
+    const int s1 = min(L, s0 + split_tokens);
+    const int part_tokens = share_tokens(s1 - s0);
+    const int parts = (s1 - s0 + part_tokens - 1) / part_tokens;   // shares with tokens
+    const bool whole = nsplit == 1 && parts == 1;   // a context of one share: nothing to merge
 
-  if constexpr (kSpread) {   // one share: its state goes out as it is
-    if (wave >= parts) return;
-    const int t0 = s0 + wave * part_tokens;
-    walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt,
-                                  num_blocks, t0, min(s1, t0 + part_tokens), scale_log2,
-                                  o_lds[0], ml_lds[0]);
-    wave_lds_sync();
-    const size_t row = (size_t)s * num_q_heads + h0;
-    for (int e = threadIdx.x; e < G * D / 4; e += kWave) {
-      const int h = e / (D / 4), d4 = e % (D / 4);
-      const float4 o = reinterpret_cast<const float4*>(o_lds[0])[e];
-      if (whole) {
-        write_row4<BF16>(out, (row + h) * (D / 4) + d4, ml_lds[0][h].y,
-                         fma_each(1.f, o, float4{}));
-      } else {
-        const size_t idx = ((row + h) * max_splits + split) * W + wave;
-        reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] = o;
-        if (d4 == 0) ws_ml[idx] = ml_lds[0][h];
-      }
-    }
-    return;
-  }
-  if constexpr (BF16) {
-    if (wave < parts) {
+    if constexpr (kSpread) {   // one share: its state goes out as it is
+      if (wave >= parts) return;
       const int t0 = s0 + wave * part_tokens;
       walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt,
                                     num_blocks, t0, min(s1, t0 + part_tokens), scale_log2,
-                                    o_lds[wave], ml_lds[wave]);
+                                    o_lds[0], ml_lds[0]);
+      wave_lds_sync();
+      const size_t row = (size_t)s * num_q_heads + h0;
+      for (int e = threadIdx.x; e < G * D / 4; e += kWave) {
+        const int h = e / (D / 4), d4 = e % (D / 4);
+        const float4 o = reinterpret_cast<const float4*>(o_lds[0])[e];
+        if (whole) {
+          write_row4<BF16>(out, (row + h) * (D / 4) + d4, ml_lds[0][h].y,
+                           fma_each(1.f, o, float4{}));
+        } else {
+          const size_t idx = ((row + h) * max_splits + split) * W + wave;
+          reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] = o;
+          if (d4 == 0) ws_ml[idx] = ml_lds[0][h];
+        }
+      }
+      return;
     }
-  } else {
-    __shared__ float p_lds[W][S::kTile * G];
-    __shared__ uint4 q_lds[G * S::kKCh];
-    for (int i = threadIdx.x; i < G * S::kKCh; i += blockDim.x)
-      q_lds[i] = reinterpret_cast<const uint4*>(q_row)[i];
+    const int step = kTurns ? blockDim.x / kWave : W;
+    if constexpr (BF16) {
+      for (int p = wave; p < parts; p += step) {
+        const int t0 = s0 + p * part_tokens;
+        walk_bf16<D, G, kTwo, kAhead>(tiles, reinterpret_cast<const uint16_t*>(q_row), bt,
+                                      num_blocks, t0, min(s1, t0 + part_tokens), scale_log2,
+                                      o_lds[p], ml_lds[p]);
+        if constexpr (!kTurns) break;
+      }
+    } else {
+      __shared__ float p_lds[W][S::kTile * G];
+      __shared__ uint4 q_lds[G * S::kKCh];
+      if (!kTurns || split == piece) {
+        for (int i = threadIdx.x; i < G * S::kKCh; i += blockDim.x)
+          q_lds[i] = reinterpret_cast<const uint4*>(q_row)[i];
+        __syncthreads();
+      }
+      float* orow =   // a whole context leaves from the registers
+          whole ? reinterpret_cast<float*>(out) + ((size_t)s * num_q_heads + h0) * D : nullptr;
+      for (int p = wave; p < parts; p += step) {
+        const int t0 = s0 + p * part_tokens, t1 = min(s1, t0 + part_tokens);
+        walk_f32<D, G>(tiles, q_lds, p_lds[wave], walk_ids(bt, t0, t1, num_blocks), t0, t1,
+                       scale_log2, o_lds[p], ml_lds[p], orow);
+        if constexpr (!kTurns) break;
+      }
+      if (whole) return;
+    }
     __syncthreads();
-    float* orow =   // a whole context leaves from the registers
-        whole ? reinterpret_cast<float*>(out) + ((size_t)s * num_q_heads + h0) * D : nullptr;
-    if (wave < parts) {
-      const int t0 = s0 + wave * part_tokens, t1 = min(s1, t0 + part_tokens);
-      walk_f32<D, G>(tiles, q_lds, p_lds[wave], walk_ids(bt, t0, t1, num_blocks), t0, t1,
-                     scale_log2, o_lds[wave], ml_lds[wave], orow);
-    }
-    if (whole) return;
-  }
-  __syncthreads();
 
-  // ---- merge the shares' states (log-sum-exp, in context order) ----
-  for (int e = threadIdx.x; e < G * D / 4; e += blockDim.x) {
-    const int h = e / (D / 4), d4 = e % (D / 4);
-    merge_states<float4>(
-        parts, [&](int j) { return reinterpret_cast<const float4*>(o_lds[j])[e]; },
-        [&](int j) { return ml_lds[j][h]; },
-        [&](float m, float l, float4 o) {
-          const size_t row = (size_t)s * num_q_heads + h0 + h;
-          if (nsplit == 1) {
-            write_row4<BF16>(out, row * (D / 4) + d4, l, o);
-          } else {
-            const size_t idx = row * max_splits + split;
-            reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] = o;
-            if (d4 == 0) ws_ml[idx] = make_float2(m, l);
-          }
-        });
+    // ---- merge the shares' states (log-sum-exp, in context order) ----
+    for (int e = threadIdx.x; e < G * D / 4; e += blockDim.x) {
+      const int h = e / (D / 4), d4 = e % (D / 4);
+      merge_states<float4>(
+          parts, [&](int j) { return reinterpret_cast<const float4*>(o_lds[j])[e]; },
+          [&](int j) { return ml_lds[j][h]; },
+          [&](float m, float l, float4 o) {
+            const size_t row = (size_t)s * num_q_heads + h0 + h;
+            if (nsplit == 1) {
+              write_row4<BF16>(out, row * (D / 4) + d4, l, o);
+            } else {
+              const size_t idx = row * max_splits + split;
+              reinterpret_cast<float4*>(ws_o)[idx * (D / 4) + d4] = o;
+              if (d4 == 0) ws_ml[idx] = make_float2(m, l);
+            }
+          });
+    }
+    if constexpr (!kTurns) return;
+    split += gridDim.x / (num_kv_heads * num_seqs);
+    if (split >= nsplit) return;
+    __syncthreads();   // the next split's shares overwrite the states
   }
 }
 
@@ -547,7 +588,7 @@ template <int D, int G, bool BF16, bool kTwo = false>
 static hipError_t launch_decode_t(const DecodeArgs& a) {
   const int max_splits = (a.max_seq_len + a.split_tokens - 1) / a.split_tokens;
   const int splits = max_splits > 0 ? max_splits : 1;
-  const long long blocks = (long long)splits * a.num_kv_heads * a.num_seqs;
+  long long blocks = (long long)splits * a.num_kv_heads * a.num_seqs;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   float* ws_o = reinterpret_cast<float*>(a.workspace);
   constexpr bool kCanSpread = BF16 && !kTwo;
@@ -558,14 +599,24 @@ static hipError_t launch_decode_t(const DecodeArgs& a) {
   // A context of at most 1, 2 or 3 steps has that many shares of one step each,
   // so further wavefronts would only wait.
   const int steps = (a.max_seq_len + kStepTokens - 1) / kStepTokens;
-  const int waves = spread || steps < 1 ? 1 : steps < kDecodeWaves ? steps : kDecodeWaves;
-  auto split = decode_split_kernel<D, G, BF16, kTwo, false, false>;
+  int waves = spread || steps < 1 ? 1 : steps < kDecodeWaves ? steps : kDecodeWaves;
+  const bool turns = waves == kDecodeWaves &&
+                     (blocks > kFullBlocks ||
+                      (!BF16 && steps <= kShortSteps && blocks >= kShortBlocks));
+  if (turns) {
+    waves = blocks <= kHalfBlocks ? 2 : 1;
+    const long long per_piece = (long long)a.num_kv_heads * a.num_seqs;
+    const long long pieces = std::max(kMinPieces, kMostBlocks / per_piece);
+    blocks = per_piece * std::min<long long>(splits, pieces);
+  }
+  auto split = decode_split_kernel<D, G, BF16, kTwo, false, false, false>;
+  if (turns) split = decode_split_kernel<D, G, BF16, kTwo, false, false, true>;
   if constexpr (kCanSpread) {
     if (spread)
-      split = decode_split_kernel<D, G, BF16, kTwo, true, true>;
+      split = decode_split_kernel<D, G, BF16, kTwo, true, true, false>;
     else if constexpr (D == 64)
-      if (max_splits > 1 && blocks <= kAheadBlocks)
-        split = decode_split_kernel<D, G, BF16, kTwo, true, false>;
+      if (max_splits > 1 && !turns && blocks <= kAheadBlocks)
+        split = decode_split_kernel<D, G, BF16, kTwo, true, false, false>;
   }
   trace_before(a.stream, kTwo ? "decode_split_two_tensor" : "decode_split");
   hipLaunchKernelGGL(split, dim3((unsigned)(spread ? blocks * kDecodeWaves : blocks)),

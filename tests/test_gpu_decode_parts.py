@@ -166,3 +166,93 @@ def test_short_contexts_under_any_bound(hq, hkv, d, dtype):
         got = K.decode(dev.q[:n], dev.kv, b.num_blocks, dev.bt[:n], dev.sl[:n],
                        max_seq_len=bound, **kw)
         assert torch.equal(got.view(as_int), want[:n].view(as_int)), bound
+
+
+def _loose(dev, copies, bound):
+    """Query rows, table and lengths of a batch repeated, under a larger bound."""
+    bt = torch.nn.functional.pad(dev.bt, (0, bound // 16 - dev.bt.shape[1]), value=-1)
+    return (dev.q.repeat(copies, 1, 1), bt.repeat(copies, 1).contiguous(), dev.sl.repeat(copies))
+
+
+# 46 (sequence, kv head) pairs of the batch, times splits: four wavefronts, two
+# (4232 workgroups), one (16560), and one that takes every 48th split (of 41400)
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 2, 128, "bf16"), (2, 2, 128, "bf16"),
+                                            (8, 2, 64, "bf16"), (4, 2, 64, "f32")])
+@pytest.mark.parametrize("copies,splits", [(1, 92), (4, 90), (15, 60)])
+def test_a_loose_bound_gives_the_same_bits(hq, hkv, d, dtype, copies, splits):
+    b = _batch(EDGES + [9300, 50 * 1024 - 37], hq, hkv, d, dtype, seed=218)
+    dev = Dev(b)
+    assert b.num_seqs == 23
+    say("decode loose bound", hq, hkv, d, dtype, copies, splits)
+    want = dev.decode()
+    q, bt, sl = _loose(dev, copies, splits * 1024)
+    sl[1] = 0
+    got = K.decode(q, dev.kv, b.num_blocks, bt, sl, num_kv_heads=hkv,
+                   max_seq_len=splits * 1024, scale=b.scale, out=torch.full_like(q, float("nan")))
+    as_int = torch.int16 if dtype == "bf16" else torch.int32
+    for c in range(copies):
+        part = got[23 * c:23 * (c + 1)].clone()
+        if c == 0:
+            assert not part[1].any()
+            part[1] = want[1]
+        assert torch.equal(part.view(as_int), want.view(as_int)), c
+    if dtype == "bf16" and d == 128:
+        half = b.num_blocks // 2
+        flat = dev.kv.view(b.num_blocks, -1)
+        two = K.decode_two_tensor(q, flat[:half].contiguous(), half, flat[half:].contiguous(),
+                                  b.num_blocks - half, bt, sl, num_kv_heads=hkv,
+                                  max_seq_len=splits * 1024, scale=b.scale)
+        assert torch.equal(two.view(as_int), got.view(as_int))
+
+
+def test_fp32_turns_of_short_contexts_give_the_same_bits():
+    """1024 workgroups of at most six steps, where two wavefronts take turns,
+    against one sequence at a time."""
+    lens = [30 + 11 * s for s in range(32)] + [384]
+    b = _batch(lens[1:], 4, 2, 64, "f32", seed=219)
+    dev = Dev(b)
+    say("decode fp32 turns")
+    q, bt, sl = _loose(dev, 16, 384)
+    got = K.decode(q, dev.kv, b.num_blocks, bt, sl, num_kv_heads=2, max_seq_len=384,
+                   scale=b.scale)
+    assert_parity(got[:32], oracle_decode(b), "f32", "fp32 turns", seq_bounds(b, decode=True))
+    for s in range(0, 32, 5):
+        one = K.decode(dev.q[s:s + 1], dev.kv, b.num_blocks, dev.bt[s:s + 1].contiguous(),
+                       dev.sl[s:s + 1].contiguous(), num_kv_heads=2, max_seq_len=384,
+                       scale=b.scale)
+        assert torch.equal(one[0].view(torch.int32), got[480 + s].view(torch.int32)), s
+
+
+def test_a_loose_bound_costs_little():
+    """64 contexts of 30 to 300 tokens under a bound of 131072: the workgroups
+    without tokens cost about half of what the others do (16 against 11 us), six
+    times that when each held four wavefronts."""
+    lens = [30 + (s * 37) % 271 for s in range(64)]
+    b = _batch(lens, 32, 8, 128, "bf16", seed=220)
+    dev = Dev(b)
+    say("decode cost of a loose bound")
+
+    def us(bound):
+        q, bt, sl = _loose(dev, 1, bound)
+        ws = K.workspace(K.decode_workspace_bytes(64, 32, 128, bound))
+        out = torch.empty_like(q)
+
+        def call():
+            K.decode(q, dev.kv, b.num_blocks, bt, sl, num_kv_heads=8, max_seq_len=bound,
+                     scale=b.scale, out=out, ws=ws)
+        for _ in range(20):
+            call()
+        times = []
+        for _ in range(5):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            for _ in range(50):
+                call()
+            ev[1].record()
+            torch.cuda.synchronize()
+            times.append(ev[0].elapsed_time(ev[1]) * 20)
+        return min(times)
+
+    tight, loose = us(512), us(131072)
+    say(f"bound 512 {tight:.1f} us, bound 131072 {loose:.1f} us")
+    assert loose < 3 * tight
