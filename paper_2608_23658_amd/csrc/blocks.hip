@@ -2,11 +2,17 @@
 // caller drains the elastic block-id range before decommitting it (the
 // paper, Section 3 "Controller": decommitting first drains the elastic blocks,
 // syncs, then unmaps). One workgroup per (pair, layer), bound by HBM: 1024
-// threads with four 16-byte non-temporal loads each in flight take a 64 KiB
-// block in one go (every byte is read and written once). 190 blocks of 64 KiB in
-// 32 layers, 797 MB: 138 us, 5.8 TB/s; 512 threads with eight loads 140, 256
-// with eight 148, 256 with one load at a time, as it was, 160 (5.0 TB/s, what a
-// large plain copy gets on this card).
+// threads with four 16-byte non-temporal loads each in flight take 64 KiB in one
+// go (every byte is read and written once), and what is left of a block, or a
+// smaller block, in one go too, with the chunks past its end left out. 190 blocks
+// in 32 layers, other blocks each time, against 256 threads with one cached load
+// at a time:
+//   64 KiB (797 MB)   159 -> 140 us, 5.7 TB/s     16 KiB   40.6 -> 36.1 us
+//   32 KiB           79.4 -> 73.4 us              96 KiB    121 -> 108 us
+// (with the rest of a block one cached load at a time 79.7, 42.1 and 119 us on the
+// last three). Workgroups per 16 or 32 KiB of a block gain up to 6% at 32 and 96
+// KiB and lose 4% at 64; 512 threads with eight loads 140 against 138, 256 with
+// eight 148 (64 KiB, the same blocks over and over).
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -34,7 +40,14 @@ __global__ __launch_bounds__(kCopyThreads) void copy_blocks_kernel(
 #pragma unroll
     for (int k = 0; k < kCopyUnroll; ++k) store_nt(to + i + k * kCopyThreads, v[k]);
   }
-  for (; i < n16; i += kCopyThreads) to[i] = from[i];
+  if (i >= n16) return;
+  uint4 v[kCopyUnroll];
+#pragma unroll
+  for (int k = 0; k < kCopyUnroll; ++k)
+    if (i + k * kCopyThreads < n16) v[k] = load_nt(from + i + k * kCopyThreads);
+#pragma unroll
+  for (int k = 0; k < kCopyUnroll; ++k)
+    if (i + k * kCopyThreads < n16) store_nt(to + i + k * kCopyThreads, v[k]);
 }
 
 hipError_t launch_copy_blocks(const CopyArgs& a) {

@@ -149,6 +149,17 @@ def test_prefill_step_m0_is_saved_and_restored(disassembly):
         assert not [i for i, _ in ins if i.startswith("scratch_")], name
 
 
+def test_block_copy_streams_every_size(disassembly):
+    """Every 16-byte load and store of the block copy is non-temporal, those of a
+    block's rest below 64 KiB too, and the rest's four loads are all issued
+    before its first store."""
+    (ins,) = _functions(disassembly, "copy_blocks_kernel", operands=True).values()
+    data = [(mn, ops) for mn, ops in ins if re.match(r"global_(load|store)_dwordx4", mn)]
+    assert len(data) == 16 and all(ops.endswith("nt") for _, ops in data), data
+    kinds = "".join("L" if "load" in mn else "S" for mn, _ in data)
+    assert kinds == "LLLLSSSS" * 2, kinds
+
+
 def test_no_kernel_spills_registers(disassembly):
     """Every kernel in the library fits its registers: a spill would put
     scratch loads and stores (counted by vmcnt) into the pipelines."""
