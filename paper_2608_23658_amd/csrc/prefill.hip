@@ -294,9 +294,12 @@ __device__ __forceinline__ int2 row_pieces(int L, int C) {
   return make_int2(per, (L - 1) / per + 1);
 }
 
-// Exclusive prefix sum of v over the workgroup; *total gets the sum and *flags
-// the number of threads with flag set.
-__device__ __forceinline__ int plan_scan(int v, bool flag, int2* lds, int* total, int* flags) {
+// Exclusive prefix sum of v over the workgroup, its total, and the number of
+// threads with flag set.
+struct PlanScan {
+  int before, total, set_total;
+};
+__device__ __forceinline__ PlanScan plan_scan(int v, bool flag, int2* lds) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   int x = v;
 #pragma unroll
@@ -307,18 +310,38 @@ __device__ __forceinline__ int plan_scan(int v, bool flag, int2* lds, int* total
   const int set = __popcll(__ballot(flag));
   if (lane == kWave - 1) lds[wave] = make_int2(x, set);
   __syncthreads();
-  int before = 0, all = 0, count = 0;
+  PlanScan r = {x - v, 0, 0};
 #pragma unroll
   for (int w = 0; w < kPlanThreads / kWave; ++w) {
     const int2 e = lds[w];
-    before += w < wave ? e.x : 0;
-    all += e.x;
-    count += e.y;
+    r.before += w < wave ? e.x : 0;
+    r.total += e.x;
+    r.set_total += e.y;
   }
   __syncthreads();
-  *total = __builtin_amdgcn_readfirstlane(all);
-  *flags = __builtin_amdgcn_readfirstlane(count);
-  return before + x - v;
+  r.total = __builtin_amdgcn_readfirstlane(r.total);
+  r.set_total = __builtin_amdgcn_readfirstlane(r.set_total);
+  return r;
+}
+
+// Sums and maxima over the workgroup, in one order whatever the timing: a
+// wavefront's by its fixed tree, then the wavefronts' one after another.
+struct PlanTotals {
+  float steps, tokens;           // sums: they only feed estimates
+  float max_steps, max_tokens;
+};
+__device__ __forceinline__ PlanTotals plan_totals(PlanTotals v, PlanTotals* lds) {
+  v = {wave_sum(v.steps), wave_sum(v.tokens), wave_max(v.max_steps), wave_max(v.max_tokens)};
+  if (threadIdx.x % kWave == 0) lds[threadIdx.x / kWave] = v;
+  __syncthreads();
+  PlanTotals r = lds[0];
+#pragma unroll
+  for (int w = 1; w < kPlanThreads / kWave; ++w) {
+    const PlanTotals e = lds[w];
+    r = {r.steps + e.steps, r.tokens + e.tokens, fmaxf(r.max_steps, e.max_steps),
+         fmaxf(r.max_tokens, e.max_tokens)};
+  }
+  return r;
 }
 
 // Tile t of a chunk of sequences: its sequence's index in the chunk, first row,
@@ -344,9 +367,9 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
   __shared__ int first[kPlanThreads + 1];     // first tile of each sequence of the chunk
   __shared__ int2 scan_lds[kPlanThreads / kWave];
   __shared__ int hist[256], row_hist[256], steps[kPlanThreads];
-  __shared__ float sum_steps, sum_tokens;
-  __shared__ int max_steps, max_tokens, num_rows, extra_row_items, next_slot, next_split, next_row_slot,
-      next_row_split, row_slots_needed;
+  __shared__ PlanTotals totals_lds[kPlanThreads / kWave];
+  __shared__ int extra_row_items, next_slot, next_split, next_row_slot, next_row_split,
+      row_slots_needed;
   __shared__ int cand_items[kPlanCandidates], cand_slots[kPlanCandidates];
   __shared__ PlanChoice choice;
   const int tid = threadIdx.x;
@@ -376,12 +399,11 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
       row = a.rows && r.y - r.x == 1;
       nt = row ? 0 : (r.y - r.x + R - 1) / R;
     }
-    int2 total;
-    const int at = plan_scan(nt, row, scan_lds, &total.x, &total.y);
-    first[tid] = at;
-    if (tid == 0) first[kPlanThreads] = total.x;
+    const PlanScan at = plan_scan(nt, row, scan_lds);
+    first[tid] = at.before;
+    if (tid == 0) first[kPlanThreads] = at.total;
     __syncthreads();
-    return total;   // tiles and one-row sequences
+    return at;   // of tiles and one-row sequences
   };
   // The rows of a sequence are taken in descending order.
   auto tile_of = [&](int t) {
@@ -401,11 +423,6 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
   };
 
   if (tid == 0) {
-    sum_steps = 0.f;
-    sum_tokens = 0.f;
-    num_rows = 0;
-    max_steps = 1;
-    max_tokens = 1;
     extra_row_items = 0;
     next_slot = 0;
     next_split = 0;
@@ -417,15 +434,16 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
     hist[tid] = 0;
     row_hist[tid] = 0;
   }
-  const int2 found = load_chunk(0);   // its barriers also publish the zeros above
+  const PlanScan found = load_chunk(0);   // its barriers also publish the zeros above
   // tiles (of all kv heads) that run at once, one workgroup per CU
   const int lanes = max(1, kNumCUs / a.num_kv_heads);
-  int chunk_tiles = kResident ? min(found.x, kPlanThreads) : found.x, all_tiles = chunk_tiles;
+  int chunk_tiles = kResident ? min(found.total, kPlanThreads) : found.total;
+  int all_tiles = chunk_tiles, all_rows = found.set_total;
   PlanTile own = {0, 0, 0};
   if constexpr (kResident) {
     if (tid < chunk_tiles) own = tile_of(tid);
     steps[tid] = own.N;
-    if (a.max_slots == 0 && found.y == 0 && chunk_tiles <= min(lanes, a.max_items)) {
+    if (a.max_slots == 0 && all_rows == 0 && chunk_tiles <= min(lanes, a.max_items)) {
       // whole tiles that all run at once: any order does
       if (tid < chunk_tiles)
         a.items[tid] = {own.idx, own.q0, 0, own.N, -1, seq_cu[own.idx], seq_n[own.idx],
@@ -441,10 +459,12 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
       if (tid < chunk_tiles) tile(0, own);
       if (a.rows && tid < a.num_seqs && seq_n[tid] == 1) row(tid, seq_cu[tid], seq_L[tid]);
     } else {
-      all_tiles = 0;
+      all_tiles = all_rows = 0;
       for (int base = 0; base < a.num_seqs; base += kPlanThreads) {
-        chunk_tiles = load_chunk(base).x;
+        const PlanScan chunk = load_chunk(base);
+        chunk_tiles = chunk.total;
         all_tiles += chunk_tiles;
+        all_rows += chunk.set_total;
         for (int t = tid; t < chunk_tiles; t += kPlanThreads) tile(base, tile_of(t));
         if (a.rows && base + tid < a.num_seqs && seq_n[tid] == 1)
           row(base + tid, seq_cu[tid], seq_L[tid]);
@@ -453,39 +473,21 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
     }
   };
 
-  // ---- totals (in fp32: they only feed estimates) ----
-  {
-    float st = 0.f, mx = 0.f, tok = 0.f, tok_mx = 0.f, nr = 0.f;
-    each(
-        [&](int, const PlanTile& t) {
-          st += t.N;
-          mx = fmaxf(mx, t.N);
-        },
-        [&](int, int, int L) {
-          nr += 1.f;
-          tok += L;
-          tok_mx = fmaxf(tok_mx, L);
-        });
-    st = wave_sum(st);
-    mx = wave_max(mx);
-    nr = wave_sum(nr);
-    if (tid % kWave == 0) {
-      atomicAdd(&sum_steps, st);
-      atomicMax(&max_steps, (int)mx);
-    }
-    if (nr > 0.f) {
-      tok = wave_sum(tok);
-      tok_mx = wave_max(tok_mx);
-      if (tid % kWave == 0) {
-        atomicAdd(&sum_tokens, tok);
-        atomicMax(&max_tokens, (int)fminf(tok_mx, 1e9f));
-        atomicAdd(&num_rows, (int)nr);
-      }
-    }
-  }
-  __syncthreads();
-  const int tiles = all_tiles, longest = max_steps, rows = num_rows;
-  const float steps_sum = sum_steps, tokens_sum = sum_tokens;
+  // ---- totals ----
+  PlanTotals sum = {0.f, 0.f, 1.f, 1.f};
+  each(
+      [&](int, const PlanTile& t) {
+        sum.steps += t.N;
+        sum.max_steps = fmaxf(sum.max_steps, t.N);
+      },
+      [&](int, int, int L) {
+        sum.tokens += L;
+        sum.max_tokens = fmaxf(sum.max_tokens, L);
+      });
+  sum = plan_totals(sum, totals_lds);
+  const int tiles = all_tiles, rows = all_rows;
+  const int longest = (int)sum.max_steps, max_tokens = (int)fminf(sum.max_tokens, 1e9f);
+  const float steps_sum = sum.steps, tokens_sum = sum.tokens;
   constexpr int kWhole = 0x7fffffff;
 
   // ---- one-row sequences: at least two items per CU, whole above that ----
@@ -588,14 +590,15 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
         atomicAdd(&row_hist[row_bucket(p.x)], p.y);
       });
   __syncthreads();
-  int total, row_total = 0, unused;
-  const int at = plan_scan(tid < 256 ? hist[tid] : 0, false, scan_lds, &total, &unused);
+  const PlanScan at = plan_scan(tid < 256 ? hist[tid] : 0, false, scan_lds);
+  const int total = at.total;
+  int row_total = 0;
   if (rows) {
-    const int row_at =
-        plan_scan(tid < 256 ? row_hist[tid] : 0, false, scan_lds, &row_total, &unused);
-    if (tid < 256) row_hist[tid] = row_at;
+    const PlanScan row_at = plan_scan(tid < 256 ? row_hist[tid] : 0, false, scan_lds);
+    row_total = row_at.total;
+    if (tid < 256) row_hist[tid] = row_at.before;
   }
-  if (tid < 256) hist[tid] = at;
+  if (tid < 256) hist[tid] = at.before;
   __syncthreads();
   // ---- one list in the order of planned starts ----
   // Tile item j starts at (j / x) dt, one-row item k at (k / y) dd (times in

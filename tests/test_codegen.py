@@ -160,6 +160,18 @@ def test_block_copy_streams_every_size(disassembly):
     assert kinds == "LLLLSSSS" * 2, kinds
 
 
+def test_prefill_plan_sums_in_a_fixed_order(disassembly):
+    """The plan's estimates choose how a step is split, and with it the last bits
+    of its rows, so its sums of lengths are added in one order on every run: no
+    floating-point atomic, whose order is that of arrival."""
+    fns = _functions(disassembly, "prefill_plan_kernel")
+    assert len(fns) == 2, sorted(fns)
+    for name, ins in fns.items():
+        found = sorted({i for i in ins if re.search(r"(add|min|max)(_rtn)?_f(32|64)", i)
+                        and re.match(r"(ds|global|flat|buffer)_", i)})
+        assert not found, (name, found)
+
+
 def test_no_kernel_spills_registers(disassembly):
     """Every kernel in the library fits its registers: a spill would put
     scratch loads and stores (counted by vmcnt) into the pipelines."""
