@@ -1436,12 +1436,15 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
   const long long tile_wgs = (long long)(a.total_q_tokens / kRowsPerTile) * a.num_kv_heads;
   const long long chip = tile_wgs > kNumCUs ? (tile_wgs + kNumCUs - 1) / kNumCUs * kNumCUs : kNumCUs;
   const bool few = a.max_seq_len > 8 * kKeys && tile_wgs < 4 * kNumCUs;
-  const bool share = few && (steps > 64 || steps * (chip - tile_wgs) > 16 * chip);
+  // The plan of more than kPlanThreads sequences or tiles takes several passes and
+  // shares no tiles: no slots for it, and no merge.
+  const long long bound = (long long)a.total_q_tokens / kRowsPerTile + a.num_seqs;
+  const bool resident = a.num_seqs <= kPlanThreads && bound <= kPlanThreads;
+  const bool share = resident && few && (steps > 64 || steps * (chip - tile_wgs) > 16 * chip);
   // Several sequences may hold one-row ones (only the device knows), one does if
   // it is one row; with one longer sequence the kernel without that branch runs.
   const bool rows = a.num_seqs > 1 || a.total_q_tokens == 1;
   const bool planned = a.workspace_bytes >= w.total && (rows || share);
-  const long long bound = (long long)a.total_q_tokens / kRowsPerTile + a.num_seqs;
   const int2* tiles = nullptr;
   const int* count;
   const PrefillItem* items = nullptr;
@@ -1474,7 +1477,6 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
     items = p.items;
     count = &p.head->items;
     trace_before(a.stream, "prefill_plan");
-    const bool resident = a.num_seqs <= kPlanThreads && bound <= kPlanThreads;
     hipLaunchKernelGGL(resident ? prefill_plan_kernel<true> : prefill_plan_kernel<false>, dim3(1),
                        dim3(kPlanThreads), 0, a.stream, p);
   } else {

@@ -98,3 +98,25 @@ def test_a_workspace_below_the_tile_list_is_refused():
     with pytest.raises(K.KvAttnError) as e:
         Dev(b).prefill(ws=torch.empty(_list_bytes(b) - 1, dtype=torch.uint8, device="cuda"))
     assert e.value.code == K.KV_ERR_INVALID
+
+
+def _kernels(call):
+    with K.KernelTrace(8) as tr:
+        call()
+    torch.cuda.synchronize()
+    return tr.names
+
+
+def test_a_plan_of_several_passes_launches_no_merge_for_tiles():
+    """600 one-row sequences of up to 1500 tokens: the plan shares no tiles above
+    512 sequences, and one-row ones only from 2048 tokens on, so nothing can
+    leave partials."""
+    n = [1] * 600
+    b = make_batch_from_lens([1 + (s * 7) % 120 for s in range(599)] + [1500], n, dtype="bf16",
+                             num_q_heads=4, num_kv_heads=1, head_dim=128, block_size=16, seed=310)
+    d = Dev(b)
+    say("prefill several passes, no merge")
+    out = {}
+    names = _kernels(lambda: out.update(o=d.prefill()))
+    assert names == ["prefill_plan", "prefill"], names
+    assert_parity(out["o"], oracle_prefill(b), "bf16", "600 rows", seq_bounds(b))
