@@ -294,10 +294,9 @@ __device__ __forceinline__ int2 row_pieces(int L, int C) {
   return make_int2(per, (L - 1) / per + 1);
 }
 
-// Exclusive prefix sum of v over the workgroup, its total, and the number of
-// threads with flag set.
+// Exclusive prefix sums of v and of flag over the workgroup, and their totals.
 struct PlanScan {
-  int before, total, set_total;
+  int before, total, set_before, set_total;
 };
 __device__ __forceinline__ PlanScan plan_scan(int v, bool flag, int2* lds) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -307,15 +306,16 @@ __device__ __forceinline__ PlanScan plan_scan(int v, bool flag, int2* lds) {
     const int y = __shfl_up(x, o, kWave);
     x += lane >= o ? y : 0;
   }
-  const int set = __popcll(__ballot(flag));
-  if (lane == kWave - 1) lds[wave] = make_int2(x, set);
+  const unsigned long long set = __ballot(flag);
+  if (lane == kWave - 1) lds[wave] = make_int2(x, (int)__popcll(set));
   __syncthreads();
-  PlanScan r = {x - v, 0, 0};
+  PlanScan r = {x - v, 0, (int)__popcll(set & ((1ull << lane) - 1)), 0};
 #pragma unroll
   for (int w = 0; w < kPlanThreads / kWave; ++w) {
     const int2 e = lds[w];
     r.before += w < wave ? e.x : 0;
     r.total += e.x;
+    r.set_before += w < wave ? e.y : 0;
     r.set_total += e.y;
   }
   __syncthreads();
@@ -360,7 +360,10 @@ struct PlanChoice {
 // and each thread keeps its tile in registers over all passes: 5.5 us, 7.2 with
 // candidates to weigh and 12 with one-row sequences to mix in, where finding the
 // tiles again in each pass and one thread weighing the candidates took 10.3 and
-// 15.1 for the first two; the tile map takes 4.7.
+// 15.1 for the first two; the tile map takes 4.7. A call that runs in one round
+// needs no order: it is written at once, also with one-row sequences (143 rows with
+// 16 of them under 814 tokens, 8 query heads over 8: 23.8 -> 19.8 us; 9 of 176 over
+// 692 with 2, 32 over 8: 39.5 -> 35.0).
 template <bool kResident>
 __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs args) {
   __shared__ int seq_cu[kPlanThreads], seq_n[kPlanThreads], seq_L[kPlanThreads];
@@ -440,15 +443,22 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
   int chunk_tiles = kResident ? min(found.total, kPlanThreads) : found.total;
   int all_tiles = chunk_tiles, all_rows = found.set_total;
   PlanTile own = {0, 0, 0};
+  // Whole tiles and one-row sequences that all run at once, in any order.
+  const bool one_round = kResident && chunk_tiles + all_rows <= min(lanes, a.max_items);
+  auto write_whole = [&] {
+    if (tid < chunk_tiles)
+      a.items[tid] = {own.idx, own.q0, 0, own.N, -1, seq_cu[own.idx], seq_n[own.idx],
+                      seq_L[own.idx]};
+    if (a.rows && tid < a.num_seqs && seq_n[tid] == 1)
+      a.items[chunk_tiles + found.set_before] = {tid, -1, 0, seq_L[tid], -1, seq_cu[tid], 1,
+                                                 seq_L[tid]};
+    if (tid == 0) *a.head = {chunk_tiles + all_rows, 0, 0, 0};
+  };
   if constexpr (kResident) {
     if (tid < chunk_tiles) own = tile_of(tid);
     steps[tid] = own.N;
-    if (a.max_slots == 0 && all_rows == 0 && chunk_tiles <= min(lanes, a.max_items)) {
-      // whole tiles that all run at once: any order does
-      if (tid < chunk_tiles)
-        a.items[tid] = {own.idx, own.q0, 0, own.N, -1, seq_cu[own.idx], seq_n[own.idx],
-                        seq_L[own.idx]};
-      if (tid == 0) *a.head = {chunk_tiles, 0, 0, 0};
+    if (one_round && a.max_slots == 0 && a.max_row_slots == 0) {
+      write_whole();
       return;
     }
   }

@@ -120,3 +120,29 @@ def test_a_plan_of_several_passes_launches_no_merge_for_tiles():
     names = _kernels(lambda: out.update(o=d.prefill()))
     assert names == ["prefill_plan", "prefill"], names
     assert_parity(out["o"], oracle_prefill(b), "bf16", "600 rows", seq_bounds(b))
+
+
+def _plan_head(ws):
+    """Items, shared tiles and shared one-row sequences of the call that used ws."""
+    torch.cuda.synchronize()
+    return tuple(ws[:12].view(torch.int32).tolist())
+
+
+# tiles and one-row sequences that fit one round, at its edge (32 workgroups'
+# worth at 8 kv heads), and one more; sequences without new rows among them
+@pytest.mark.parametrize("rows", [5, 26, 27])
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (8, 8)])
+def test_one_round_of_tiles_and_one_row_sequences(rows, hq, hkv):
+    R = 32 * 8 * hkv // hq
+    L = [2 * R + 70, 40, R] + [3 + 29 * s for s in range(rows)] + [9]
+    n = [2 * R + 1, 0, R] + [1] * rows + [2]
+    b = make_batch_from_lens(L, n, dtype="bf16", num_q_heads=hq, num_kv_heads=hkv, head_dim=128,
+                             block_size=16, seed=311)
+    assert b.max_seq_len <= 1024
+    d = Dev(b)
+    ws = K.workspace(K.prefill_workspace_bytes(b.num_seqs, b.total_q_tokens, hq, 128))
+    ws.fill_(0xff)
+    say("prefill one round", rows, hq, hkv)
+    out = d.prefill(ws=ws, out=torch.full_like(d.q, float("nan")))
+    assert _plan_head(ws) == (5 + rows, 0, 0)
+    assert_parity(out, oracle_prefill(b), "bf16", f"one round {rows} {hq}/{hkv}", seq_bounds(b))
