@@ -277,6 +277,31 @@ struct PlanArgs {
   PrefillPlan* head;
 };
 
+// Whether sharing tiles can gain more than it costs, for a call whose longest
+// tile walks this many key steps and whose tiles are this many workgroups: below
+// eight steps an item's own cost outweighs what it saves, four or more rounds of
+// tiles gain nothing, and up to 64 steps the longest walk, over the part of the
+// last round that is idle, has to be min_steps. The host asks with its bounds
+// whether the wider plan and the merge are worth a launch. 32 query heads over 8,
+// whole tiles, shared, and not shared by that rule:
+//   2 of 770 rows over 50                         36 / 38 / 33 us
+//   9 of 176 over 692, with 2 one-row             38 / 46 / 35 us
+//   440 rows over 227                             29 / 31 / 27 us
+// and shared by it: 53 -> 41 us (1673 rows with 15 one-row, 8 query heads over 8).
+// With a loose bound it launches them, and the plan asks whether to weigh
+// candidates, with the lengths. Not shared / shared, under a bound of 131072 (the
+// longest walk over the idle part): 512 rows over 256 (9.0) 29.8 / 32.2 us, 200
+// over 512 (10.5) 28.5 / 27.1, 1024 over 256 (10.0) 41.9 / 39.5, 1024 over 1024
+// (16.0) 59.3 / 53.3.
+constexpr int kLaunchSteps = 16, kPlanSteps = 10;
+__host__ __device__ __forceinline__ bool sharing_pays(long long steps, long long workgroups,
+                                                      int min_steps) {
+  const long long chip = workgroups > kNumCUs ? (workgroups + kNumCUs - 1) / kNumCUs * kNumCUs
+                                              : kNumCUs;
+  return steps > 8 && workgroups < 4 * kNumCUs &&
+         (steps > 64 || steps * (chip - workgroups) >= min_steps * chip);
+}
+
 // Steps per item and items of a tile of N steps, at most C steps per item.
 __device__ __forceinline__ int2 tile_pieces(int N, int C) {
   const int p = (N - 1) / C + 1;
@@ -502,21 +527,28 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
 
   // ---- one-row sequences: at least two items per CU, whole above that ----
   int row_c = kWhole, row_items = rows;
-  if (rows > 0 && a.max_row_slots > 0) {
+  if (rows > 0 && a.max_row_slots > 0)
     row_c = max(kRowTokens, ((int)fminf(tokens_sum / (2 * lanes), 1e9f) / 512 + 1) * 512);
-    if (max_tokens > row_c) {
-      each([](int, const PlanTile&) {},
-           [&](int, int, int L) {
-             const int p = row_pieces(L, row_c).y;
-             if (p > 1) {
-               atomicAdd(&row_slots_needed, p);
-               atomicAdd(&extra_row_items, p - 1);
-             }
-           });
-      __syncthreads();
-      if (row_slots_needed > a.max_row_slots) row_c = kWhole;
-      else row_items += extra_row_items;
+  const bool share = kResident && a.max_slots > 0 &&
+                     sharing_pays(longest, (long long)tiles * a.num_kv_heads, kPlanSteps);
+  if constexpr (kResident) {
+    if (one_round && !share && max_tokens <= row_c) {
+      write_whole();
+      return;
     }
+  }
+  if (max_tokens > row_c) {
+    each([](int, const PlanTile&) {},
+         [&](int, int, int L) {
+           const int p = row_pieces(L, row_c).y;
+           if (p > 1) {
+             atomicAdd(&row_slots_needed, p);
+             atomicAdd(&extra_row_items, p - 1);
+           }
+         });
+    __syncthreads();
+    if (row_slots_needed > a.max_row_slots) row_c = kWhole;
+    else row_items += extra_row_items;
   }
   const float row_steps = tokens_sum / 64.f;
   const float row_work = kRowStep * row_steps + (float)kItemSteps * row_items;
@@ -527,9 +559,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
   // estimated as r rounds of its items on the fewest CUs that do them in r
   // rounds, while the one-row items run on the others as far as those and HBM
   // allow, and the rest of them after; without one-row items r is as few as
-  // fit. The fewest items within 3% of the best win. A step with four or more
-  // rounds of tiles gains nothing and is not shared.
-  const bool share = kResident && a.max_slots > 0 && tiles < 4 * lanes;
+  // fit. The fewest items within 3% of the best win.
   PlanChoice pick = {kWhole, 1, 0, 1.f, 1.f};   // whole tiles, nothing to mix
   if (share || rows) {
     constexpr int kPer = kPlanThreads / kPlanCandidates;   // 32 lanes per candidate
@@ -582,6 +612,12 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs arg
     }
     __syncthreads();
     pick = choice;
+    if constexpr (kResident) {
+      if (one_round && !rows && pick.limit == kWhole) {
+        write_whole();
+        return;
+      }
+    }
   }
   const int C = pick.limit;
   const float per_bucket = 255.f / max(1, min(longest, C));   // C bounds an item's steps
@@ -1431,26 +1467,15 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
   constexpr int kRowsPerTile = 32 * kWaves / G;
   uint8_t* ws = static_cast<uint8_t*>(a.workspace);
   const PrefillWs w = prefill_ws(a.num_seqs, a.total_q_tokens, G, a.num_kv_heads);
-  // Sharing tiles needs more than 8 key steps somewhere (below that an item's
-  // own cost outweighs what it saves) and fewer than four rounds of tiles. Up to
-  // 64 steps the longest walk, over the part of the last round that is idle, has
-  // to outweigh the wider plan and the merge's launch, about 16 steps a round.
-  // 32 query heads over 8, whole tiles, shared, and not shared by this rule:
-  //   2 of 770 rows over 50                         36 / 38 / 33 us
-  //   9 of 176 over 692, with 2 one-row             38 / 46 / 40 us
-  //   440 rows over 227                             29 / 31 / 27 us
-  // and shared by it: 53 -> 41 us (1673 rows with 15 one-row, 8 query heads over 8).
-  // One sequence whose tiles are not shared needs no plan either: the tile map, 1
-  // us faster, lists its tiles in the same order.
-  const long long steps = ((long long)a.max_seq_len + kKeys - 1) / kKeys;
-  const long long tile_wgs = (long long)(a.total_q_tokens / kRowsPerTile) * a.num_kv_heads;
-  const long long chip = tile_wgs > kNumCUs ? (tile_wgs + kNumCUs - 1) / kNumCUs * kNumCUs : kNumCUs;
-  const bool few = a.max_seq_len > 8 * kKeys && tile_wgs < 4 * kNumCUs;
-  // The plan of more than kPlanThreads sequences or tiles takes several passes and
-  // shares no tiles: no slots for it, and no merge.
+  // Sharing tiles is weighed here by the bounds the host knows, and by the plan,
+  // with room for the partials, by the lengths it finds. One sequence whose tiles
+  // are not shared needs no plan: the tile map, 1 us faster, lists its tiles in the
+  // same order. The plan of more than kPlanThreads sequences or tiles shares none.
   const long long bound = (long long)a.total_q_tokens / kRowsPerTile + a.num_seqs;
   const bool resident = a.num_seqs <= kPlanThreads && bound <= kPlanThreads;
-  const bool share = resident && few && (steps > 64 || steps * (chip - tile_wgs) > 16 * chip);
+  const long long steps = ((long long)a.max_seq_len + kKeys - 1) / kKeys;
+  const long long tile_wgs = (long long)(a.total_q_tokens / kRowsPerTile) * a.num_kv_heads;
+  const bool share = resident && sharing_pays(steps, tile_wgs, kLaunchSteps);
   // Several sequences may hold one-row ones (only the device knows), one does if
   // it is one row; with one longer sequence the kernel without that branch runs.
   const bool rows = a.num_seqs > 1 || a.total_q_tokens == 1;
@@ -1473,7 +1498,8 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
     // One-row sequences are shared from 1024 tokens on (a CU's walk of 4 us), from
     // 2048 where only they would need the merge's launch (about 4 us), or from
     // 8192 beside four or more rounds of tiles, which such a walk can hide in.
-    const int shared_from = share ? kRowTokens : few ? 2 * kRowTokens : 8 * kRowTokens;
+    const int shared_from = share ? kRowTokens
+                            : tile_wgs < 4 * kNumCUs ? 2 * kRowTokens : 8 * kRowTokens;
     max_row_slots = rows && a.max_seq_len > shared_from ? w.max_row_slots : 0;
     grid_items = (int)(bound + max_slots + max_row_slots);
     p.max_items = grid_items;

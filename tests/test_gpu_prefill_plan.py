@@ -146,3 +146,29 @@ def test_one_round_of_tiles_and_one_row_sequences(rows, hq, hkv):
     out = d.prefill(ws=ws, out=torch.full_like(d.q, float("nan")))
     assert _plan_head(ws) == (5 + rows, 0, 0)
     assert_parity(out, oracle_prefill(b), "bf16", f"one round {rows} {hq}/{hkv}", seq_bounds(b))
+
+
+# whether tiles are shared under a bound far above the lengths: too short to
+# share, walks that gain little, and ones that gain (10 steps of idle chip)
+@pytest.mark.parametrize("L,N,hq,hkv,shared", [([200], [200], 32, 8, False),
+                                               ([70, 90, 100], [64, 50, 100], 32, 8, False),
+                                               ([768, 300, 20], [512, 1, 1], 32, 8, False),
+                                               ([1280], [1024], 32, 8, True),
+                                               ([768, 90], [40, 1], 4, 1, True)])
+def test_a_loose_bound_shares_by_the_lengths(L, N, hq, hkv, shared):
+    b = make_batch_from_lens(L, N, dtype="bf16", num_q_heads=hq, num_kv_heads=hkv, head_dim=128,
+                             block_size=16, seed=312)
+    d = Dev(b)
+    bt = torch.nn.functional.pad(d.bt, (0, 8192 - d.bt.shape[1]), value=-1).contiguous()
+    ws = K.workspace(K.prefill_workspace_bytes(b.num_seqs, b.total_q_tokens, hq, 128))
+    ws.fill_(0xff)
+    say("prefill loose bound", L, N)
+    out = K.prefill_chunk(d.q, d.kv, b.num_blocks, bt, d.sl, d.cu, num_kv_heads=hkv,
+                          max_seq_len=131072, scale=b.scale, ws=ws,
+                          out=torch.full_like(d.q, float("nan")))
+    items, splits, row_splits = _plan_head(ws)
+    R = 32 * 8 * hkv // hq
+    whole = sum(-(-n // R) if n > 1 else 1 for n in N)
+    assert (splits > 0) == shared and row_splits == 0
+    assert items > whole if shared else items == whole
+    assert_parity(out, oracle_prefill(b), "bf16", "loose bound", seq_bounds(b))
