@@ -175,19 +175,32 @@ const char* kvattn_trace_kernel_name(int i);
  *               never changes the arithmetic
  * workspace     device scratch of kvattn_prefill_workspace_bytes(...) bytes, no
  *               initial contents needed, not used by another call in flight.
- *               About 65 MiB of it hold partial results of work tiles whose
- *               keys several workgroups share, which is how a call with few
- *               tiles fills the chip; a workspace of only
+ *               About 65 MiB of it, whatever the sizes, hold partial results
+ *               of work tiles whose keys several workgroups share, which is how
+ *               a call with few tiles fills the chip; a workspace of only
  *               align256(8 * (total_q_tokens / 32 + num_seqs + 1) + 16) bytes
  *               is accepted too and every tile is then one workgroup's
  *
  * Causal alignment is bottom-right: row i of sequence s sees keys
- * 0 .. seq_lens[s] - n_s + i. Whether a tile's keys are shared depends on the
- * whole call (its sequences, chunk sizes and lengths), so the last bits of a row
- * can differ between calls that batch it differently; calls of four or more
- * tiles per CU never share. Supported: bf16, block_size 16, head_dim 128,
- * num_q_heads / num_kv_heads in {1, 2, 4, 8}; KV_F32 returns KV_ERR_UNSUPPORTED.
- * Asynchronous; allocates nothing.
+ * 0 .. seq_lens[s] - n_s + i.
+ *
+ * The same call gives the same bits again. With a workspace below the planned
+ * size a row's bits depend on its own sequence alone: its tokens, chunk and
+ * length. With the planned size they also depend on the rest of the call,
+ * max_seq_len and the workspace's size included, in these ways:
+ *   - a sequence that adds one row is not a tile but takes decode's walk, unless
+ *     the call is one sequence of several rows;
+ *   - tiles may be shared, in pieces chosen for the call, if it has at most 512
+ *     sequences and 512 tiles (of 256 / group rows), max_seq_len > 512 and
+ *     total_q_tokens / (256 / group) * num_kv_heads < 1024 (four tiles per CU);
+ *   - one-row sequences longer than 1024 tokens may be shared, in pieces whose
+ *     size follows from all of the call's, if max_seq_len > 1024 where tiles may
+ *     be shared, > 2048 in other calls of fewer than four tiles per CU, and
+ *     > 8192 beside four or more.
+ *
+ * Supported: bf16, block_size 16, head_dim 128, num_q_heads / num_kv_heads in
+ * {1, 2, 4, 8}; KV_F32 returns KV_ERR_UNSUPPORTED. Asynchronous; allocates
+ * nothing.
  */
 size_t kvattn_prefill_workspace_bytes(int num_seqs, int total_q_tokens, int num_q_heads,
                                       int head_dim);

@@ -172,3 +172,41 @@ def test_a_loose_bound_shares_by_the_lengths(L, N, hq, hkv, shared):
     assert (splits > 0) == shared and row_splits == 0
     assert items > whole if shared else items == whole
     assert_parity(out, oracle_prefill(b), "bf16", "loose bound", seq_bounds(b))
+
+
+def test_the_least_workspace_gives_a_sequences_own_bits():
+    """With room for the list of whole tiles only, a row's bits depend on its own
+    sequence: alone under its own length as the bound, or in a batch under a
+    larger one, one-row sequences included."""
+    L, N = [4096, 2111, 9000, 640, 70, 300], [33, 65, 1, 200, 9, 1]
+    b = make_batch_from_lens(L, N, dtype="bf16", num_q_heads=8, num_kv_heads=2, head_dim=128,
+                             block_size=16, seed=314)
+    d = Dev(b)
+    ws = K.workspace(_list_bytes(b))
+    say("prefill least workspace")
+    whole = d.prefill(ws=ws)
+    assert_parity(whole, oracle_prefill(b), "bf16", "least workspace", seq_bounds(b))
+    for s in range(len(L)):
+        lo, hi = int(b.cu_seqlens_q[s]), int(b.cu_seqlens_q[s + 1])
+        cu = torch.tensor([0, hi - lo], dtype=torch.int32, device="cuda")
+        one = K.prefill_chunk(d.q[lo:hi], d.kv, b.num_blocks, d.bt[s:s + 1].contiguous(),
+                              d.sl[s:s + 1].contiguous(), cu, num_kv_heads=2, max_seq_len=L[s],
+                              scale=b.scale, ws=ws)
+        assert torch.equal(one.view(torch.int16), whole[lo:hi].view(torch.int16)), s
+
+
+def test_beside_four_rounds_of_tiles_rows_are_shared_and_tiles_are_not():
+    """1024 workgroups of tiles: their rows have the bits of whole tiles; a one-row
+    sequence above 8192 tokens is shared all the same."""
+    b = make_batch_from_lens([4096, 9000, 700], [4096, 1, 1], dtype="bf16", num_q_heads=64,
+                             num_kv_heads=8, head_dim=128, block_size=16, seed=315)
+    d = Dev(b)
+    ws = K.workspace(K.prefill_workspace_bytes(b.num_seqs, b.total_q_tokens, 64, 128))
+    say("prefill four rounds")
+    out = torch.empty_like(d.q)
+    assert _kernels(lambda: d.prefill(ws=ws, out=out)) == ["prefill_plan", "prefill", "prefill_combine"]
+    assert _plan_head(ws)[1:] == (0, 1)
+    least = d.prefill(ws=K.workspace(_list_bytes(b)))
+    assert torch.equal(out[:4096].view(torch.int16), least[:4096].view(torch.int16))
+    ref = oracle_prefill(b, seqs=[1, 2])
+    assert_parity(out[4096:], ref[4096:], "bf16", "rows beside four rounds", [0, 1, 2])
