@@ -1,6 +1,7 @@
 """Planned prefill steps: tiles whose keys are shared by several workgroups and
-merged, items ordered over sequences, one-row sequences beside tiles. Against the oracle on every row, and
-against the same call with a workspace that only holds the list of whole tiles."""
+merged, items ordered over sequences, one-row sequences beside tiles. Against the
+oracle on every row, with the kernels launched and what the plan shares, and the
+same call with a workspace that only holds the list of whole tiles."""
 import pytest
 import torch
 
@@ -21,7 +22,27 @@ def _list_bytes(b):
     return ((b.total_q_tokens // 32 + b.num_seqs + 1) * 8 + 16 + 255) // 256 * 256
 
 
-def _check(L, N, hq, hkv, seed):
+def _kernels(call):
+    with K.KernelTrace(8) as tr:
+        call()
+    torch.cuda.synchronize()
+    return tr.names
+
+
+def _plan_head(ws):
+    """Items, shared tiles and shared one-row sequences of the call that used ws."""
+    torch.cuda.synchronize()
+    return tuple(ws[:12].view(torch.int32).tolist())
+
+
+MAP = ["prefill_tile_map", "prefill"]
+PLAN = ["prefill_plan", "prefill"]
+MERGE = PLAN + ["prefill_combine"]
+
+
+def _check(L, N, hq, hkv, seed, names, shared=False, shared_rows=0):
+    """Against the oracle, with the kernels the call launches, whether the plan
+    shares tiles and how many one-row sequences it shares (None: some)."""
     b = make_batch_from_lens(L, N, dtype="bf16", num_q_heads=hq, num_kv_heads=hkv,
                              head_dim=128, block_size=16, seed=seed)
     d = Dev(b)
@@ -29,11 +50,15 @@ def _check(L, N, hq, hkv, seed):
     ws.fill_(0xff)                     # no initial contents are needed
     say("prefill planned", L[:4], N[:4], hq, hkv)
     ref = oracle_prefill(b)
-    for what, w in (("planned", ws), ("planned again", ws),
-                    ("whole tiles", K.workspace(_list_bytes(b)))):
+    for what, w, kernels in (("planned", ws, names), ("planned again", ws, names),
+                             ("whole tiles", K.workspace(_list_bytes(b)), MAP)):
         assert w is ws or w.numel() < ws.numel()
-        out = d.prefill(ws=w, out=torch.full_like(d.q, float("nan")))
-        torch.cuda.synchronize()
+        out = torch.full_like(d.q, float("nan"))
+        assert _kernels(lambda: d.prefill(ws=w, out=out)) == kernels, what
+        if kernels is not MAP:
+            _, splits, row_splits = _plan_head(w)
+            assert (splits > 0) == shared, (what, splits)
+            assert row_splits == shared_rows if shared_rows is not None else row_splits > 0, what
         assert_parity(out, ref, "bf16", f"{what} {hq}/{hkv}", seq_bounds(b))
 
 
@@ -41,21 +66,32 @@ def _check(L, N, hq, hkv, seed):
 # one row; a length that ends inside a block; a sequence too short to share
 @pytest.mark.parametrize("hq,hkv", [(8, 1), (4, 1), (2, 1), (1, 1), (12, 3), (32, 8), (64, 8)])
 def test_shared_tiles(hq, hkv):
-    _check([4096, 2111, 640, 70], [33, 65, 200, 9], hq, hkv, seed=301)
+    _check([4096, 2111, 640, 70], [33, 65, 200, 9], hq, hkv, 301, MERGE, shared=True)
 
 
 @pytest.mark.parametrize("hq,hkv", [(32, 8), (8, 8)])
 def test_one_short_chunk_over_a_long_context(hq, hkv):
-    _check([6351], [201], hq, hkv, seed=302)
+    _check([6351], [201], hq, hkv, 302, MERGE, shared=True)
 
 
 def test_more_sequences_than_one_planning_pass_holds():
     n = [1 + s % 3 for s in range(1100)]
-    _check([x + s % 130 for s, x in enumerate(n)], n, 4, 1, seed=303)
+    _check([x + s % 130 for s, x in enumerate(n)], n, 4, 1, 303, PLAN)
 
 
 def test_more_tiles_than_threads_plan_at_once():
-    _check([17600, 900], [17600, 700], 8, 1, seed=304)
+    _check([17600, 900], [17600, 700], 8, 1, 304, MERGE)
+
+
+def test_rows_shared_in_several_planning_passes():
+    """One-row sequences long enough to be shared in each of the plan's passes of
+    512 sequences, among short ones and a chunk of more rows."""
+    L = [1 + (s * 7) % 120 for s in range(1100)]
+    n = [1] * 1100
+    for s, x in ((10, 3000), (511, 4000), (512, 1025), (700, 9000), (1099, 5000)):
+        L[s] = x
+    L[520], n[520] = 900, 200
+    _check(L, n, 4, 1, 313, MERGE, shared_rows=5)
 
 
 # one-row sequences: shared by several items, up to a split's edges, one token;
@@ -64,20 +100,21 @@ def test_more_tiles_than_threads_plan_at_once():
 @pytest.mark.parametrize("tiles", [False, True])
 def test_one_row_sequences(hq, hkv, tiles):
     L = [9000, 1, 63, 512, 513, 1024, 1025, 4097] + ([2500, 300] if tiles else [])
-    _check(L, [1] * 8 + ([130, 3] if tiles else []), hq, hkv, seed=306)
+    _check(L, [1] * 8 + ([130, 3] if tiles else []), hq, hkv, 306, MERGE, shared=tiles,
+           shared_rows=3)
 
 
-# both sides of the rules by which a call shares tiles (17 steps with the chip
-# nearly idle) and one-row sequences (2048 tokens)
-@pytest.mark.parametrize("L,N,hq,hkv", [([1024], [300], 8, 1), ([1089], [300], 8, 1),
-                                        ([1100, 2048], [1100, 1], 32, 8),
-                                        ([1100, 2049], [1100, 1], 32, 8)])
-def test_share_rule_edges(L, N, hq, hkv):
-    _check(L, N, hq, hkv, seed=309)
+# both sides of the rules by which a call may share tiles (16 steps with the chip
+# nearly idle are 15.4 of it) and one-row sequences (2048 tokens)
+@pytest.mark.parametrize("L,N,hq,hkv,names,shared_rows", [
+    ([1024], [300], 8, 1, MAP, 0), ([1025], [300], 8, 1, MERGE, 0),
+    ([1100, 2048], [1100, 1], 32, 8, PLAN, 0), ([1100, 2049], [1100, 1], 32, 8, MERGE, 1)])
+def test_share_rule_edges(L, N, hq, hkv, names, shared_rows):
+    _check(L, N, hq, hkv, 309, names, shared=L == [1025], shared_rows=shared_rows)
 
 
 def test_a_single_row():
-    _check([5000], [1], 8, 2, seed=307)
+    _check([5000], [1], 8, 2, 307, MERGE, shared_rows=1)
 
 
 def test_a_one_row_sequence_without_context_gives_zeros():
@@ -100,13 +137,6 @@ def test_a_workspace_below_the_tile_list_is_refused():
     assert e.value.code == K.KV_ERR_INVALID
 
 
-def _kernels(call):
-    with K.KernelTrace(8) as tr:
-        call()
-    torch.cuda.synchronize()
-    return tr.names
-
-
 def test_a_plan_of_several_passes_launches_no_merge_for_tiles():
     """600 one-row sequences of up to 1500 tokens: the plan shares no tiles above
     512 sequences, and one-row ones only from 2048 tokens on, so nothing can
@@ -120,12 +150,6 @@ def test_a_plan_of_several_passes_launches_no_merge_for_tiles():
     names = _kernels(lambda: out.update(o=d.prefill()))
     assert names == ["prefill_plan", "prefill"], names
     assert_parity(out["o"], oracle_prefill(b), "bf16", "600 rows", seq_bounds(b))
-
-
-def _plan_head(ws):
-    """Items, shared tiles and shared one-row sequences of the call that used ws."""
-    torch.cuda.synchronize()
-    return tuple(ws[:12].view(torch.int32).tolist())
 
 
 # tiles and one-row sequences that fit one round, at its edge (32 workgroups'
@@ -204,7 +228,7 @@ def test_beside_four_rounds_of_tiles_rows_are_shared_and_tiles_are_not():
     ws = K.workspace(K.prefill_workspace_bytes(b.num_seqs, b.total_q_tokens, 64, 128))
     say("prefill four rounds")
     out = torch.empty_like(d.q)
-    assert _kernels(lambda: d.prefill(ws=ws, out=out)) == ["prefill_plan", "prefill", "prefill_combine"]
+    assert _kernels(lambda: d.prefill(ws=ws, out=out)) == MERGE
     assert _plan_head(ws)[1:] == (0, 1)
     least = d.prefill(ws=K.workspace(_list_bytes(b)))
     assert torch.equal(out[:4096].view(torch.int16), least[:4096].view(torch.int16))
