@@ -53,8 +53,10 @@
 // many short ones keeps that many workgroups. The shares and merges are the same,
 // and so are the bits. A call at four wavefronts always / by these rules (the
 // workgroups of its bound):
-//   128 sequences of 30 to 500, bound 4096 (4096)      26 us (two: 27.5, one: 29)
-//   256 of 512 to 4096, bound 4096 (8192)              363 / 362 us
+//   256 sequences of 512 to 4096, bound 4096 (8192)    387 us (two: 389)
+//   6 of 700 to 131071, bound 131071 (6144)            140.5 us (two: 143)
+//   64 of 30 to 300, bound 16384 (8192)                16 us (two: 14)
+//   256 of 1000 to 16000, bound 16000 (32768)          1280 / 1288 us
 //   256 of 30 to 300, bound 8192 (16384)               43 / 34 us (one: 35.5)
 //   256 of 30 to 300, bound 16384 (32768)              59 / 38 us (two: 43)
 //   64 of 30 to 300, bound 131072 (65536)              67 / 16 us
@@ -103,7 +105,7 @@
 namespace kvattn {
 
 constexpr long long kAheadBlocks = 1024;
-constexpr long long kFullBlocks = 4096, kHalfBlocks = 16384, kMostBlocks = 32768;
+constexpr long long kFullBlocks = 8192, kHalfBlocks = 16384, kMostBlocks = 32768;
 constexpr long long kMinPieces = 48;
 constexpr int kShortSteps = 6, kShortBlocks = 1024;   // fp32
 

@@ -175,10 +175,10 @@ def _loose(dev, copies, bound):
 
 
 # 46 (sequence, kv head) pairs of the batch, times splits: four wavefronts, two
-# (4232 workgroups), one (16560), and one that takes every 48th split (of 41400)
+# (8280 workgroups), one (16560), and one that takes every 48th split (of 41400)
 @pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 2, 128, "bf16"), (2, 2, 128, "bf16"),
                                             (8, 2, 64, "bf16"), (4, 2, 64, "f32")])
-@pytest.mark.parametrize("copies,splits", [(1, 92), (4, 90), (15, 60)])
+@pytest.mark.parametrize("copies,splits", [(1, 178), (1, 180), (4, 90), (15, 60)])
 def test_a_loose_bound_gives_the_same_bits(hq, hkv, d, dtype, copies, splits):
     b = _batch(EDGES + [9300, 50 * 1024 - 37], hq, hkv, d, dtype, seed=218)
     dev = Dev(b)
