@@ -205,7 +205,12 @@ __global__ __launch_bounds__(256) void prefill_tile_map_kernel(const int* __rest
 //   1024 rows over 1024                                             62 -> 53 us
 //   9 chunks of 100 to 900 rows over 1000 to 8000 tokens           443 -> 367 us
 //   8192 rows over 24576 (four even rounds, not shared)           3274, 3278 us
-
+// Items go by length over all sequences. Of 15 steps of 3 to 20 chunks that share
+// nothing, 13 gain up to 11% by it against sequence by sequence or stay, and two of
+// sequences alike lose 5%: 9 chunks of 300 to 600 rows over 1500 to 3000 tokens, 64
+// query heads over 8, 306 -> 323 us, 9 of 113 to 679 over 1722 to 3445 275 -> 289.
+// Coarser lengths (8 or 32 classes instead of 256) give 2% back on the first and
+// lose up to 3% on others.
 //
 // A sequence that adds one row (a decode sequence in a unified step) is no tile:
 // its tile would put one row of each head through 32-row products and stage its
