@@ -387,13 +387,12 @@ struct PlanChoice {
 
 // Latency-bound, one workgroup ahead of the attention kernel. kResident: the
 // sequences fit one chunk (512) and their tiles one per thread, the usual case,
-// and each thread keeps its tile in registers over all passes: 5.5 us, 7.2 with
-// candidates to weigh and 12 with one-row sequences to mix in, where finding the
-// tiles again in each pass and one thread weighing the candidates took 10.3 and
-// 15.1 for the first two; the tile map takes 4.7. A call that runs in one round
-// needs no order: it is written at once, also with one-row sequences (143 rows with
-// 16 of them under 814 tokens, 8 query heads over 8: 23.8 -> 19.8 us; 9 of 176 over
-// 692 with 2, 32 over 8: 39.5 -> 35.0).
+// and each thread keeps its tile in registers over all passes. A call that runs in
+// one round needs no order and is written at once, also with one-row sequences: 2.5
+// us (rocprof), as the tile map. Ordering takes 5.4, candidates to weigh or one-row
+// sequences to mix in 7.1, both 10.0. A call of 143 rows with 16 one-row sequences
+// under 814 tokens, 8 query heads over 8, took 23.8 us with the ordering passes and
+// takes 19.8, 9 of 176 over 692 with 2, 32 over 8, 39.5 and 35.0.
 template <bool kResident>
 __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs args) {
   __shared__ int seq_cu[kPlanThreads], seq_n[kPlanThreads], seq_L[kPlanThreads];
@@ -1474,8 +1473,9 @@ static hipError_t launch_prefill_t(const PrefillArgs& a) {
   const PrefillWs w = prefill_ws(a.num_seqs, a.total_q_tokens, G, a.num_kv_heads);
   // Sharing tiles is weighed here by the bounds the host knows, and by the plan,
   // with room for the partials, by the lengths it finds. One sequence whose tiles
-  // are not shared needs no plan: the tile map, 1 us faster, lists its tiles in the
-  // same order. The plan of more than kPlanThreads sequences or tiles shares none.
+  // are not shared needs no plan: the tile map lists its tiles in the same order
+  // without the passes that order several. The plan of more than kPlanThreads
+  // sequences or tiles shares none.
   const long long bound = (long long)a.total_q_tokens / kRowsPerTile + a.num_seqs;
   const bool resident = a.num_seqs <= kPlanThreads && bound <= kPlanThreads;
   const long long steps = ((long long)a.max_seq_len + kKeys - 1) / kKeys;
